@@ -255,7 +255,7 @@ struct SortStreams {
 };
 
 int sort_by_cell(hipStream_t st, const SortStreams &caller, const SortStreams &tmp, int64_t n,
-                 int32_t n_cells, const BinScratch &bs, const int *gate)
+                 int32_t n_cells, const BinScratch &bs, DevFlags *f)
 {
     const int bits = ceil_log2(n_cells);
     if (bits == 0 || n <= 1) return PIC_OK;
@@ -284,7 +284,8 @@ int sort_by_cell(hipStream_t st, const SortStreams &caller, const SortStreams &t
         p.bits = per;
         if (p.shift + p.bits > bits) p.bits = bits - p.shift;
         if (p.bits <= 0) p.bits = 1;
-        p.gate = gate;
+        p.gate = &f->unsorted;
+        p.done = &f->sort_done[ps];
         RC(radix_pass(p, bs, st));
     }
     return PIC_OK;
@@ -736,7 +737,6 @@ int pic_bin_cells(pic_ctx *c, const int32_t *cell_of, int64_t n, int32_t n_cells
     uint32_t *iB = (uint32_t *)b.take(4 * (size_t)n);
     BinScratch bs;
     bs.hist = (uint32_t *)b.take(radix_scratch_bytes(n));
-    bs.bsum = bs.hist + 256 * ((n + 4095) / 4096 + 1);   // block sums follow the histogram
     RC(launch_reset_flags(c->flags, c->stream));
     const int bits = ceil_log2(n_cells);
     const int32_t *sorted_keys = cell_of;
@@ -758,6 +758,7 @@ int pic_bin_cells(pic_ctx *c, const int32_t *cell_of, int64_t n, int32_t n_cells
             p.n = n;
             p.shift = 0;
             p.bits = 1;
+            p.done = &c->flags->sort_done[0];
             RC(radix_pass(p, bs, c->stream));
             sorted_keys = kA;
         }
@@ -775,6 +776,7 @@ int pic_bin_cells(pic_ctx *c, const int32_t *cell_of, int64_t n, int32_t n_cells
             p.bits = per;
             if (p.shift + p.bits > bits) p.bits = bits - p.shift;
             if (p.bits <= 0) p.bits = 1;
+            p.done = &c->flags->sort_done[ps];
             RC(radix_pass(p, bs, c->stream));
             sorted_keys = p.key_out;
         }
@@ -838,7 +840,6 @@ static int step_enqueue(pic_ctx *c, const StepArgs &s, hipStream_t st, const uin
     void *tv = b.take((size_t)n * 3 * es);
     BinScratch bs;
     bs.hist = (uint32_t *)b.take(radix_scratch_bytes(n));
-    bs.bsum = bs.hist + 256 * ((n + 4095) / 4096 + 1);
     set_huge_scratch(dtype, n, b.take(huge_scratch_bytes(dtype, n)));
     // the re-binning buffers are free again by the collide pass: the
     // segmented path of the largest cells copies members into them
@@ -875,7 +876,7 @@ static int step_enqueue(pic_ctx *c, const StepArgs &s, hipStream_t st, const uin
                 tmp.p64[k] = (uint64_t *)tv + (size_t)k * n;
             }
         }
-        RC(sort_by_cell(st, caller, tmp, n, n_cells, bs, &c->flags->unsorted));
+        RC(sort_by_cell(st, caller, tmp, n, n_cells, bs, c->flags));
         RC(launch_bin_check(s.cell_of, n, n_cells, cs, c->flags, 0, &c->flags->unsorted, st));
         ktime_end(KT_SORT, st);
     }

@@ -16,12 +16,14 @@
 
 namespace {
 
-constexpr int RS_THREADS = 256;   // radix kernels: 4 waves
-constexpr int RS_ITEMS = 16;      // rounds per tile
-constexpr int RS_TILE = RS_THREADS * RS_ITEMS;
-constexpr int SCAN_THREADS = 1024;
-constexpr int SCAN_ITEMS = 8;
-constexpr int SCAN_CHUNK = SCAN_THREADS * SCAN_ITEMS;
+constexpr int RS_T = 1024;                    // threads of the sort's kernels
+constexpr int RS_K = 4;                       // elements per thread and tile
+constexpr int RS_TILE = RS_T * RS_K;
+constexpr int RS_WAVES = RS_T / PIC_WAVE;
+constexpr int RS_PER_WAVE = RS_TILE / RS_WAVES;
+constexpr int RS_DIGITS = 256;                // largest radix
+constexpr int RS_MAX_BLOCKS = 512;            // two workgroups per CU
+static_assert(RS_K * PIC_WAVE * RS_WAVES == RS_TILE, "tile split");
 
 __global__ void k_reset_flags(DevFlags *f)
 {
@@ -30,6 +32,7 @@ __global__ void k_reset_flags(DevFlags *f)
         f->range_err = 0;
         f->huge_total = 0;
         f->seg_fallback = 0;
+        for (int k = 0; k < 4; ++k) f->sort_done[k] = 0;
     }
     if (threadIdx.x < 8) {
         f->head[threadIdx.x] = 0;
@@ -68,20 +71,28 @@ __global__ void k_step_inc(uint64_t *s)
 // Position i in [0, n] is the boundary between element i-1 and i: every cell
 // id j in (cell_of[i-1], cell_of[i]] starts at i, so with sorted input each
 // entry of cell_start is written exactly once (empty cells included).  Each
-// thread takes four consecutive positions (one 16-byte load when aligned).
-__global__ void k_bin_check(const int32_t *__restrict__ cell_of, int64_t n, int32_t n_cells,
-                            int32_t *__restrict__ cell_start, DevFlags *f, int set_unsorted,
-                            const int *gate)
+// thread takes four consecutive positions (one 16-byte load when aligned), the
+// id before them comes from the lane below.  Bound by the read of cell_of
+// (4.7 TB/s on 40.96M sorted ids).  A workgroup reports at most once, and only
+// what is not reported yet: with one atomic per wave on the same word a check
+// of 16M ids out of order took 350 us, most of it waiting for that word; now 20.
+constexpr int BC_T = 256;
+
+__global__ __launch_bounds__(BC_T) void k_bin_check(const int32_t *__restrict__ cell_of, int64_t n,
+                                                    int32_t n_cells, int32_t *__restrict__ cell_start,
+                                                    DevFlags *f, int set_unsorted, const int *gate)
 {
+    __shared__ int s_bad[BC_T / PIC_WAVE], s_uns[BC_T / PIC_WAVE];
     if (gate && *gate == 0) return;
+    const int lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
     int bad = 0, uns = 0;
     const int64_t nq = n / 4 + 1;
     const bool vec = ((uintptr_t)cell_of & 15u) == 0;
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < nq;
-         q += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i0 = q * 4;
+    const int64_t stride = (int64_t)gridDim.x * BC_T;
+    // whole waves take part in every round (the shuffle below)
+    for (int64_t q0 = blockIdx.x * (int64_t)BC_T + wid * PIC_WAVE; q0 < nq; q0 += stride) {
+        const int64_t i0 = (q0 + lane) * 4;
         int32_t c[5];
-        c[0] = i0 > 0 ? cell_of[i0 - 1] : -1;
         if (vec && i0 + 4 <= n) {
             const int4 x = *(const int4 *)(cell_of + i0);
             c[1] = x.x;
@@ -92,6 +103,10 @@ __global__ void k_bin_check(const int32_t *__restrict__ cell_of, int64_t n, int3
 #pragma unroll
             for (int j = 0; j < 4; ++j) c[1 + j] = i0 + j < n ? cell_of[i0 + j] : n_cells;
         }
+        int32_t first = -1;   // the id before the wave's first position
+        if (lane == 0 && i0 > 0) first = cell_of[i0 - 1];
+        c[0] = __shfl_up(c[4], 1, PIC_WAVE);
+        if (lane == 0) c[0] = first;
         bool out[4], desc = false;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -116,25 +131,26 @@ __global__ void k_bin_check(const int32_t *__restrict__ cell_of, int64_t n, int3
         }
     }
     const uint64_t wb = __ballot(bad), wu = __ballot(uns);
-    if ((threadIdx.x & (PIC_WAVE - 1)) == 0) {
-        if (wb) {
-            atomicOr(&f->range_err, 1);
-            atomicOr(&f->sticky_range, 1);
-        }
-        if (wu && set_unsorted) {
-            atomicOr(&f->unsorted, 1);
-            if (set_unsorted == 2) atomicOr(&f->sticky_state, 1);
-        }
+    if (lane == 0) {
+        s_bad[wid] = wb != 0;
+        s_uns[wid] = wu != 0;
     }
-}
-
-__global__ void k_copy32(uint32_t *__restrict__ dst, const uint32_t *__restrict__ src, int64_t n,
-                         const int *gate)
-{
-    if (gate && *gate == 0) return;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        dst[i] = src[i];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    int any_bad = 0, any_uns = 0;
+    for (int w = 0; w < BC_T / PIC_WAVE; ++w) {
+        any_bad |= s_bad[w];
+        any_uns |= s_uns[w];
+    }
+    if (any_bad) {
+        atomicOr(&f->range_err, 1);
+        atomicOr(&f->sticky_range, 1);
+    }
+    if (any_uns && set_unsorted &&
+        __hip_atomic_load(&f->unsorted, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+        if (set_unsorted == 2) atomicOr(&f->sticky_state, 1);
+        atomicOr(&f->unsorted, 1);
+    }
 }
 
 __device__ __forceinline__ uint32_t digit_of(int32_t key, int shift, int bits)
@@ -142,280 +158,273 @@ __device__ __forceinline__ uint32_t digit_of(int32_t key, int shift, int bits)
     return ((uint32_t)key >> shift) & ((1u << bits) - 1u);
 }
 
-// Per-tile digit counts: hist[d * nblocks + tile].
-__global__ __launch_bounds__(RS_THREADS) void k_radix_hist(RadixPass p, uint32_t *__restrict__ hist)
+// Re-binning: one least-significant-digit pass is two launches.  The tiles of
+// RS_TILE elements are split into contiguous runs, one per workgroup (at most
+// two workgroups per CU), so the digit counts to scan are few (digits x
+// workgroups, not digits x tiles) and the last workgroup to finish counting
+// scans them: no scan launches, and no launch of one workgroup per tile.  That
+// matters most when the storage is in order and all of these kernels leave at
+// once: the sort's empty launches took 41 us of a 40.96M-electron step with
+// ten launches of full grids, and take 12 us now.
+// Two passes of 16M binary32 electrons, 5% of them moved to a neighbouring
+// cell: 740 -> 345 us; of 40.96M shuffled ones: 1,690 -> 1,110 us.
+
+// One more element of digit d, counted in LDS.  In nearly sorted storage a
+// wave's elements share a digit or two: these are added by one lane each
+// (64 lanes adding to one LDS word serialise).
+__device__ __forceinline__ void count_digit(uint32_t *h, uint32_t d, bool valid)
 {
-    if (p.gate && *p.gate == 0) return;
-    __shared__ uint32_t h[256];
-    const int R = 1 << p.bits;
-    for (int d = threadIdx.x; d < R; d += RS_THREADS) h[d] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int64_t e = base + r * RS_THREADS + threadIdx.x;
-        if (e < p.n) atomicAdd(&h[digit_of(p.key_in[e], p.shift, p.bits)], 1u);
+    const int lane = threadIdx.x & (PIC_WAVE - 1);
+#pragma unroll
+    for (int peel = 0; peel < 2; ++peel) {
+        const uint64_t m = __ballot(valid);
+        if (!m) return;
+        const int leader = __ffsll((unsigned long long)m) - 1;
+        const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
+        const uint64_t same = __ballot(valid && d == d0);
+        if (lane == leader) atomicAdd(&h[d0], (uint32_t)__popcll(same));
+        valid = valid && d != d0;
     }
-    __syncthreads();
-    for (int d = threadIdx.x; d < R; d += RS_THREADS) hist[(int64_t)d * gridDim.x + blockIdx.x] = h[d];
+    if (valid) atomicAdd(&h[d], 1u);
 }
 
-// Exclusive scan of SCAN_ITEMS consecutive values per thread over the block;
-// returns the thread's exclusive prefix and (in *total) the block total.
-__device__ uint32_t block_excl_scan(uint32_t x, uint32_t *total)
-{
-    __shared__ uint32_t wtot[SCAN_THREADS / PIC_WAVE];
-    const int lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
-    const uint32_t inc = wave_incl_scan(x);
-    if (lane == PIC_WAVE - 1) wtot[wid] = inc;
-    __syncthreads();
-    uint32_t off = 0, tot = 0;
-    for (int w = 0; w < SCAN_THREADS / PIC_WAVE; ++w) {
-        if (w < wid) off += wtot[w];
-        tot += wtot[w];
-    }
-    __syncthreads();
-    *total = tot;
-    return off + inc - x;
-}
+// Digit counts of each workgroup's run of tiles, hist[d * gridDim.x + block];
+// the last workgroup turns every digit's row into an exclusive scan over the
+// workgroups and writes the digits' starts behind the rows.  The counts travel
+// in device-scope stores and loads, complete before the workgroup's arrival is
+// counted; a fence instead would write back a whole L2 per workgroup (150 us
+// when every wave issued one).
+constexpr int RC_T = 1024;
+constexpr int RC_WAIT_VM = 0x0F70;   // s_waitcnt operand: vector memory only
 
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_reduce(const uint32_t *__restrict__ a, int64_t L,
-                                                             uint32_t *__restrict__ bsum,
-                                                             const int *gate)
+__global__ __launch_bounds__(RC_T) void k_radix_count(const int32_t *__restrict__ key_in, int64_t n, int shift,
+                                                      int bits, int tiles_per_block, uint32_t *__restrict__ hist,
+                                                      unsigned int *done, const int *gate)
 {
     if (gate && *gate == 0) return;
-    const int64_t base = (int64_t)blockIdx.x * SCAN_CHUNK + threadIdx.x * SCAN_ITEMS;
-    uint32_t s = 0;
-    for (int k = 0; k < SCAN_ITEMS; ++k)
-        if (base + k < L) s += a[base + k];
-    uint32_t tot;
-    block_excl_scan(s, &tot);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
-}
-
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_top(uint32_t *__restrict__ bsum, int64_t nb,
-                                                          const int *gate)
-{
-    if (gate && *gate == 0) return;
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < nb; base += SCAN_CHUNK) {
-        const int64_t b0 = base + threadIdx.x * SCAN_ITEMS;
-        uint32_t v[SCAN_ITEMS], s = 0;
-        for (int k = 0; k < SCAN_ITEMS; ++k) {
-            v[k] = b0 + k < nb ? bsum[b0 + k] : 0u;
-            s += v[k];
+    __shared__ uint32_t h[RS_DIGITS];
+    __shared__ int s_last;
+    const int R = 1 << bits;
+    const int lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
+    if (threadIdx.x < RS_DIGITS) h[threadIdx.x] = 0u;
+    __syncthreads();
+    const int64_t beg = (int64_t)blockIdx.x * tiles_per_block * RS_TILE;
+    int64_t end = beg + (int64_t)tiles_per_block * RS_TILE;
+    end = end < n ? end : n;
+    const bool vec = ((uintptr_t)key_in & 15u) == 0;
+    for (int64_t base = beg; base < end; base += 4 * RC_T) {
+        const int64_t e = base + 4 * (int64_t)threadIdx.x;
+        int32_t k[4];
+        if (vec && e + 4 <= end) {
+            const int4 x = *(const int4 *)(key_in + e);
+            k[0] = x.x;
+            k[1] = x.y;
+            k[2] = x.z;
+            k[3] = x.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k[j] = e + j < end ? key_in[e + j] : 0;
         }
-        uint32_t tot;
-        uint32_t off = block_excl_scan(s, &tot) + carry;
-        for (int k = 0; k < SCAN_ITEMS; ++k) {
-            if (b0 + k < nb) bsum[b0 + k] = off;
-            off += v[k];
-        }
-        carry += tot;
-    }
-}
-
-__global__ __launch_bounds__(SCAN_THREADS) void k_scan_down(uint32_t *__restrict__ a, int64_t L,
-                                                           const uint32_t *__restrict__ bsum,
-                                                           const int *gate)
-{
-    if (gate && *gate == 0) return;
-    const int64_t base = (int64_t)blockIdx.x * SCAN_CHUNK + threadIdx.x * SCAN_ITEMS;
-    uint32_t v[SCAN_ITEMS], s = 0;
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        v[k] = base + k < L ? a[base + k] : 0u;
-        s += v[k];
-    }
-    uint32_t tot;
-    uint32_t off = block_excl_scan(s, &tot) + bsum[blockIdx.x];
-    for (int k = 0; k < SCAN_ITEMS; ++k) {
-        if (base + k < L) a[base + k] = off;
-        off += v[k];
-    }
-}
-
-// Stable scatter.  The tile is visited in element order, RS_THREADS elements
-// per round; within a round an element's rank among equal digits is
-// (count in earlier rounds) + (count in earlier waves) + (earlier lanes of
-// its own wave), the last found from ballots over the digit bits.
-__global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(RadixPass p,
-                                                              const uint32_t *__restrict__ offs)
-{
-    if (p.gate && *p.gate == 0) return;
-    constexpr int NW = RS_THREADS / PIC_WAVE;
-    __shared__ uint32_t base[256];
-    __shared__ uint32_t wc[NW * 256];
-    __shared__ uint32_t goff[256];
-    const int R = 1 << p.bits;
-    for (int d = threadIdx.x; d < R; d += RS_THREADS) {
-        base[d] = 0;
-        goff[d] = offs[(int64_t)d * gridDim.x + blockIdx.x];
-        for (int w = 0; w < NW; ++w) wc[w * 256 + d] = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) count_digit(h, digit_of(k[j], shift, bits), e + j < end);
     }
     __syncthreads();
-    const int lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (PIC_WAVE - lane));
-    const int64_t tile = (int64_t)blockIdx.x * RS_TILE;
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int64_t e = tile + r * RS_THREADS + threadIdx.x;
-        const bool valid = e < p.n;
-        const int32_t key = valid ? p.key_in[e] : 0;
-        const uint32_t d = digit_of(key, p.shift, p.bits);
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < p.bits; ++b) {
-            const uint64_t m = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? m : ~m;
+    const int G = gridDim.x;
+    if ((int)threadIdx.x < R)
+        __hip_atomic_store(&hist[(int64_t)threadIdx.x * G + blockIdx.x], h[threadIdx.x], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(RC_WAIT_VM);   // the counts are visible to the device
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(done, 1u) == (unsigned)(G - 1);
+    __syncthreads();
+    if (!s_last) return;
+    // one wave per digit row: all of the row's loads in flight together
+    constexpr int RU = RS_MAX_BLOCKS / PIC_WAVE;
+    for (int d = wid; d < R; d += RC_T / PIC_WAVE) {
+        uint32_t *row = hist + (int64_t)d * G;
+        uint32_t v[RU], carry = 0;
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const int g = u * PIC_WAVE + lane;
+            v[u] = g < G ? __hip_atomic_load(&row[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
         }
-        const uint32_t rank = __popcll(peers & lt);
-        if (valid && rank == 0) wc[wid * 256 + d] = __popcll(peers);
-        __syncthreads();
-        uint32_t pos = 0;
-        if (valid) {
-            pos = base[d] + rank;
-            for (int w = 0; w < wid; ++w) pos += wc[w * 256 + d];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const int g = u * PIC_WAVE + lane;
+            const uint32_t inc = wave_incl_scan_dpp(v[u]);
+            if (g < G) row[g] = carry + inc - v[u];
+            carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, PIC_WAVE - 1);
         }
-        __syncthreads();
-        for (int dd = threadIdx.x; dd < R; dd += RS_THREADS) {
-            uint32_t s = 0;
-            for (int w = 0; w < NW; ++w) {
-                s += wc[w * 256 + dd];
-                wc[w * 256 + dd] = 0;
-            }
-            base[dd] += s;
-        }
-        if (valid) {
-            const int64_t o = (int64_t)goff[d] + pos;
-            p.key_out[o] = key;
-            for (int s = 0; s < p.n32; ++s)
-                p.p32_out[s][o] = (s == p.iota_slot) ? (uint32_t)e : p.p32_in[s][e];
-            for (int s = 0; s < p.n64; ++s) p.p64_out[s][o] = p.p64_in[s][e];
-        }
-        __syncthreads();
+        if (lane == 0) h[d] = carry;
     }
-}
-
-// Stable scatter with the tile staged in LDS (tiles of RS_TILE elements, so
-// the per-tile digit counts of k_radix_hist apply).  Wave w takes elements
-// [w * 256, w * 256 + 256) of the tile in four rounds of 64; an element's rank
-// among equal digits of its wave comes from ballots over the digit bits and a
-// per-wave running count in LDS (no block barrier while ranking).  The waves'
-// counts then give each (wave, digit) its start inside the tile, every element
-// goes to its place in a digit-sorted copy of the tile in LDS, and the copy is
-// written out in slot order: consecutive slots of one digit go to consecutive
-// addresses, so the stores are coalesced runs instead of one scattered word
-// per element and array.
-constexpr int RS2_THREADS = 1024;
-constexpr int RS2_WAVES = RS2_THREADS / PIC_WAVE;
-constexpr int RS2_PER_WAVE = RS_TILE / RS2_WAVES;          // 256 elements
-constexpr int RS2_ROUNDS = RS2_PER_WAVE / PIC_WAVE;         // 4
-static_assert(RS2_ROUNDS * PIC_WAVE * RS2_WAVES == RS_TILE, "tile split");
-
-// Dynamic LDS of the staged scatter (its static part is about 21 KB).
-constexpr size_t RS2_LDS_MAX = 136 * 1024;
-
-size_t rs2_stage_bytes(int n32, int n64)
-{
-    return (size_t)RS_TILE * (4 + 4 * (size_t)n32 + 8 * (size_t)n64);
-}
-
-__global__ __launch_bounds__(RS2_THREADS) void k_radix_scatter_lds(RadixPass p,
-                                                                   const uint32_t *__restrict__ offs)
-{
-    if (p.gate && *p.gate == 0) return;
-    extern __shared__ __align__(16) unsigned char stage[];
-    __shared__ uint32_t run[RS2_WAVES * 256];   // per-wave running digit counts, then wave starts
-    __shared__ uint32_t tstart[257];            // digit starts inside the tile
-    __shared__ uint32_t goff[256];              // global start of this tile's run of each digit
-    const int R = 1 << p.bits;
-    const int lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (PIC_WAVE - lane));
-    const int64_t tile = (int64_t)blockIdx.x * RS_TILE;
-    const int64_t tn = p.n - tile < RS_TILE ? p.n - tile : RS_TILE;   // elements in this tile
-    uint32_t *skey = (uint32_t *)stage;
-    uint32_t *s32 = skey + RS_TILE;
-    uint64_t *s64 = (uint64_t *)(s32 + (size_t)p.n32 * RS_TILE);
-    for (int q = threadIdx.x; q < RS2_WAVES * 256; q += RS2_THREADS) run[q] = 0;
-    if (threadIdx.x < R) goff[threadIdx.x] = offs[(int64_t)threadIdx.x * gridDim.x + blockIdx.x];
-    // digit starts inside the tile from this tile's counts (one wave scans):
-    // the offsets are an exclusive scan over (digit, tile), so a tile's count
-    // of a digit is the next offset minus its own (the total after the last)
+    __syncthreads();
     if (wid == 0) {
-        const int64_t L = (int64_t)R * gridDim.x;
         uint32_t carry = 0;
         for (int d0 = 0; d0 < R; d0 += PIC_WAVE) {
             const int d = d0 + lane;
-            uint32_t c = 0;
-            if (d < R) {
-                const int64_t idx = (int64_t)d * gridDim.x + blockIdx.x;
-                c = (idx + 1 < L ? offs[idx + 1] : (uint32_t)p.n) - offs[idx];
+            const uint32_t c = d < R ? h[d] : 0u;
+            const uint32_t inc = wave_incl_scan_dpp(c);
+            if (d < R) hist[(int64_t)R * G + d] = carry + inc - c;
+            carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, PIC_WAVE - 1);
+        }
+    }
+}
+
+// Stable placement of the workgroup's tiles, one after another.  Wave w holds
+// elements [w * 256, w * 256 + 256) of the tile in four rounds of 64 (keys and
+// payload in registers, every load in flight before the first use); an
+// element's rank among equal digits of its wave comes from ballots over the
+// digit bits and a per-wave running count in LDS (no block barrier while
+// ranking).  The waves' counts then give each (wave, digit) its start inside
+// the tile.  The arrays pass through LDS one at a time: every element goes to
+// its place in the digit-sorted tile and the tile is written out in slot
+// order, so consecutive slots of one digit go to consecutive addresses.
+// Bound by the memory: 40 bytes per binary32 electron at 4.6 TB/s when few
+// digits meet in a tile, 3.3 TB/s when 64 digits do (runs of 64 elements).
+// Staging one array at a time (two buffers of RS_TILE entries instead of a
+// whole tile of every array) and loading the payload with the keys leaves one
+// memory round trip per tile; tiles of 2,048 on 512 threads, three workgroups
+// per CU, have runs half as long: 590 against 490 us per pass of 40.96M
+// shuffled electrons.
+template <int N32, int N64, bool IOTA>
+__global__ __launch_bounds__(RS_T) void k_radix_place(RadixPass p, int tiles_per_block,
+                                                      const uint32_t *__restrict__ hist)
+{
+    if (p.gate && *p.gate == 0) return;
+    constexpr int ES = N64 > 0 ? 8 : 4;
+    __shared__ __align__(16) unsigned char buf[2][(size_t)RS_TILE * ES];
+    __shared__ uint16_t wc[RS_WAVES * RS_DIGITS];   // per-wave digit counts, then starts in the tile
+    __shared__ uint32_t goff[RS_DIGITS];            // next output slot of each digit
+    __shared__ uint32_t tst[RS_DIGITS];             // digit starts inside the tile
+    __shared__ uint32_t dlt[RS_DIGITS];             // output slot minus slot in the tile
+    __shared__ uint32_t wsum[RS_DIGITS / PIC_WAVE];
+    const int R = 1 << p.bits, G = gridDim.x;
+    const int lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (PIC_WAVE - lane));
+    if ((int)threadIdx.x < R)
+        goff[threadIdx.x] = hist[(int64_t)R * G + threadIdx.x] + hist[(int64_t)threadIdx.x * G + blockIdx.x];
+    uint16_t *wrun = wc + wid * RS_DIGITS;
+    const int64_t ntiles = (p.n + RS_TILE - 1) / RS_TILE;
+    int64_t t_end = ((int64_t)blockIdx.x + 1) * tiles_per_block;
+    t_end = t_end < ntiles ? t_end : ntiles;
+    for (int64_t t = (int64_t)blockIdx.x * tiles_per_block; t < t_end; ++t) {
+        const int64_t tile = t * RS_TILE;
+        const int tn = (int)(p.n - tile < RS_TILE ? p.n - tile : RS_TILE);   // elements in this tile
+        int32_t key[RS_K];
+        uint32_t x32[N32][RS_K];
+        uint64_t x64[N64 > 0 ? N64 : 1][RS_K];
+        // elements past the end reload the tile's last one (not placed)
+#pragma unroll
+        for (int r = 0; r < RS_K; ++r) {
+            const int le = wid * RS_PER_WAVE + r * PIC_WAVE + lane;
+            key[r] = ld_at(p.key_in + tile, (uint32_t)(le < tn ? le : tn - 1));
+        }
+#pragma unroll
+        for (int s = 0; s < N32; ++s)
+#pragma unroll
+            for (int r = 0; r < RS_K; ++r) {
+                const int le = wid * RS_PER_WAVE + r * PIC_WAVE + lane;
+                const uint32_t i = (uint32_t)(le < tn ? le : tn - 1);
+                if constexpr (IOTA) x32[s][r] = (uint32_t)tile + i;   // one array: the element's index
+                else x32[s][r] = ld_at(p.p32_in[s] + tile, i);
             }
-            const uint32_t inc = wave_incl_scan(c);
-            if (d < R) tstart[d] = carry + inc - c;
-            carry += __shfl(inc, PIC_WAVE - 1, PIC_WAVE);
-        }
-        if (lane == 0) tstart[R] = carry;
-    }
-    // this thread's elements: round r is element wid * 256 + r * 64 + lane
-    int32_t key[RS2_ROUNDS];
-    uint32_t rank[RS2_ROUNDS];
 #pragma unroll
-    for (int r = 0; r < RS2_ROUNDS; ++r) {
-        const int64_t le = (int64_t)wid * RS2_PER_WAVE + r * PIC_WAVE + lane;
-        key[r] = le < tn ? p.key_in[tile + le] : 0;
-    }
-    __syncthreads();
-    uint32_t *wrun = run + wid * 256;
+        for (int s = 0; s < N64; ++s)
 #pragma unroll
-    for (int r = 0; r < RS2_ROUNDS; ++r) {
-        const int64_t le = (int64_t)wid * RS2_PER_WAVE + r * PIC_WAVE + lane;
-        const bool valid = le < tn;
-        const uint32_t d = digit_of(key[r], p.shift, p.bits);
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < p.bits; ++b) {
-            const uint64_t m = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? m : ~m;
-        }
-        const uint32_t before = valid ? wrun[d] : 0u;
-        rank[r] = before + __popcll(peers & lt);
-        // the group's first lane advances the wave's count (same wave: LDS
-        // operations stay in order)
-        if (valid && (peers & lt) == 0ull) wrun[d] = before + __popcll(peers);
-        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the count is in LDS
-        __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-    // wave starts per digit: tile start + the earlier waves' counts
-    for (int d = threadIdx.x; d < R; d += RS2_THREADS) {
-        uint32_t acc = tstart[d];
-        for (int w = 0; w < RS2_WAVES; ++w) {
-            const uint32_t c = run[w * 256 + d];
-            run[w * 256 + d] = acc;
-            acc += c;
-        }
-    }
-    __syncthreads();
-    // stage every element at its place in the digit-sorted tile
+            for (int r = 0; r < RS_K; ++r) {
+                const int le = wid * RS_PER_WAVE + r * PIC_WAVE + lane;
+                x64[s][r] = ld_at(p.p64_in[s] + tile, (uint32_t)(le < tn ? le : tn - 1));
+            }
 #pragma unroll
-    for (int r = 0; r < RS2_ROUNDS; ++r) {
-        const int64_t le = (int64_t)wid * RS2_PER_WAVE + r * PIC_WAVE + lane;
-        if (le < tn) {
-            const int64_t e = tile + le;
+        for (int q = 0; q < RS_WAVES * RS_DIGITS / 2 / RS_T; ++q) ((uint32_t *)wc)[threadIdx.x + q * RS_T] = 0u;
+        lds_barrier();
+        uint32_t pos[RS_K];   // rank in the wave, then slot in the tile
+#pragma unroll
+        for (int r = 0; r < RS_K; ++r) {
+            const bool valid = wid * RS_PER_WAVE + r * PIC_WAVE + lane < tn;
             const uint32_t d = digit_of(key[r], p.shift, p.bits);
-            const uint32_t q = wrun[d] + rank[r];
-            skey[q] = (uint32_t)key[r];
-            for (int s = 0; s < p.n32; ++s)
-                s32[(size_t)s * RS_TILE + q] = (s == p.iota_slot) ? (uint32_t)e : p.p32_in[s][e];
-            for (int s = 0; s < p.n64; ++s) s64[(size_t)s * RS_TILE + q] = p.p64_in[s][e];
+            uint64_t peers = __ballot(valid);
+            for (int b = 0; b < p.bits; ++b) {
+                const uint64_t m = __ballot((d >> b) & 1u);
+                peers &= ((d >> b) & 1u) ? m : ~m;
+            }
+            const uint32_t before = valid ? wrun[d] : 0u;
+            pos[r] = before + __popcll(peers & lt);
+            // the group's first lane advances the wave's count (same wave: LDS
+            // operations stay in order)
+            if (valid && (peers & lt) == 0ull) wrun[d] = (uint16_t)(before + __popcll(peers));
+            __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the count is in LDS
+            __builtin_amdgcn_wave_barrier();
         }
-    }
-    __syncthreads();
-    // write out in slot order
-    for (int q = threadIdx.x; q < tn; q += RS2_THREADS) {
-        const uint32_t k = skey[q];
-        const uint32_t d = digit_of((int32_t)k, p.shift, p.bits);
-        const int64_t o = (int64_t)goff[d] + (q - (int64_t)tstart[d]);
-        p.key_out[o] = (int32_t)k;
-        for (int s = 0; s < p.n32; ++s) p.p32_out[s][o] = s32[(size_t)s * RS_TILE + q];
-        for (int s = 0; s < p.n64; ++s) p.p64_out[s][o] = s64[(size_t)s * RS_TILE + q];
+        lds_barrier();
+        // wave starts per digit, then the digits' starts in the tile
+        uint32_t tot = 0, inc = 0;
+        if (threadIdx.x < RS_DIGITS) {
+            if ((int)threadIdx.x < R) {
+#pragma unroll
+                for (int w = 0; w < RS_WAVES; ++w) {
+                    const uint32_t c = wc[w * RS_DIGITS + threadIdx.x];
+                    wc[w * RS_DIGITS + threadIdx.x] = (uint16_t)tot;
+                    tot += c;
+                }
+            }
+            inc = wave_incl_scan(tot);
+            if (lane == PIC_WAVE - 1) wsum[wid] = inc;
+        }
+        lds_barrier();
+        if ((int)threadIdx.x < R) {
+            uint32_t off = inc - tot;
+            for (int w = 0; w < wid; ++w) off += wsum[w];
+            tst[threadIdx.x] = off;
+            dlt[threadIdx.x] = goff[threadIdx.x] - off;
+            goff[threadIdx.x] += tot;
+        }
+        lds_barrier();
+        uint32_t *k0 = (uint32_t *)buf[0];
+#pragma unroll
+        for (int r = 0; r < RS_K; ++r) {
+            const uint32_t d = digit_of(key[r], p.shift, p.bits);
+            pos[r] += tst[d] + wrun[d];
+            if (wid * RS_PER_WAVE + r * PIC_WAVE + lane < tn) k0[pos[r]] = (uint32_t)key[r];
+        }
+        lds_barrier();
+        uint32_t dst[RS_K];   // output slots of tile slots threadIdx.x + r * RS_T
+#pragma unroll
+        for (int r = 0; r < RS_K; ++r) {
+            const int q = threadIdx.x + r * RS_T;
+            dst[r] = 0u;
+            if (q < tn) {
+                const uint32_t k = k0[q];
+                dst[r] = dlt[digit_of((int32_t)k, p.shift, p.bits)] + (uint32_t)q;
+                p.key_out[dst[r]] = (int32_t)k;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < N32; ++s) {
+            uint32_t *st = (uint32_t *)buf[(s + 1) & 1];
+#pragma unroll
+            for (int r = 0; r < RS_K; ++r)
+                if (wid * RS_PER_WAVE + r * PIC_WAVE + lane < tn) st[pos[r]] = x32[s][r];
+            lds_barrier();
+#pragma unroll
+            for (int r = 0; r < RS_K; ++r) {
+                const int q = threadIdx.x + r * RS_T;
+                if (q < tn) p.p32_out[s][dst[r]] = st[q];
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < N64; ++s) {
+            uint64_t *st = (uint64_t *)buf[(N32 + s + 1) & 1];
+#pragma unroll
+            for (int r = 0; r < RS_K; ++r)
+                if (wid * RS_PER_WAVE + r * PIC_WAVE + lane < tn) st[pos[r]] = x64[s][r];
+            lds_barrier();
+#pragma unroll
+            for (int r = 0; r < RS_K; ++r) {
+                const int q = threadIdx.x + r * RS_T;
+                if (q < tn) p.p64_out[s][dst[r]] = st[q];
+            }
+        }
     }
 }
 
@@ -547,55 +556,44 @@ int launch_step_inc(uint64_t *step_dev, hipStream_t st)
 int launch_bin_check(const int32_t *cell_of, int64_t n, int32_t n_cells, int32_t *cell_start,
                      DevFlags *flags, int set_unsorted, const int *gate, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_bin_check, dim3(grid_for(n / 4 + 1, 256, 8192)), dim3(256), 0, st, cell_of, n,
+    hipLaunchKernelGGL(k_bin_check, dim3(grid_for(n / 4 + 1, BC_T, 2048)), dim3(BC_T), 0, st, cell_of, n,
                        n_cells, cell_start, flags, set_unsorted, gate);
     HIP_OK(hipGetLastError());
     return PIC_OK;
 }
 
-int launch_copy32(uint32_t *dst, const uint32_t *src, int64_t n, const int *gate, hipStream_t st)
-{
-    if (n <= 0) return PIC_OK;
-    hipLaunchKernelGGL(k_copy32, dim3(grid_for(n, 256, 8192)), dim3(256), 0, st, dst, src, n, gate);
-    HIP_OK(hipGetLastError());
-    return PIC_OK;
-}
-
+// Words of scratch of a pass: 256 digits x workgroups (at most one per tile),
+// the digits' starts behind them, and alignment.
 size_t radix_scratch_bytes(int64_t n)
 {
     const int64_t nb = (n + RS_TILE - 1) / RS_TILE + 1;
-    const int64_t L = 256 * nb;
-    const int64_t ns = (L + SCAN_CHUNK - 1) / SCAN_CHUNK + 1;
+    const int64_t L = RS_DIGITS * nb;
+    const int64_t ns = (L + 8191) / 8192 + 1;
     return (size_t)(L + ns) * sizeof(uint32_t) + 512;
 }
+
+namespace {
+template <int N32, int N64, bool IOTA>
+void place_pass(const RadixPass &p, int G, int tpb, const uint32_t *hist, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_radix_place<N32, N64, IOTA>), dim3(G), dim3(RS_T), 0, st, p, tpb, hist);
+}
+}  // namespace
 
 int radix_pass(const RadixPass &p, const BinScratch &s, hipStream_t st)
 {
     if (p.n <= 0) return PIC_OK;
-    const int64_t nb = (p.n + RS_TILE - 1) / RS_TILE;
-    const int64_t L = (int64_t)(1 << p.bits) * nb;
-    const int64_t ns = (L + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(RS_THREADS), 0, st, p, s.hist);
-    hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)ns), dim3(SCAN_THREADS), 0, st, s.hist, L, s.bsum,
-                       p.gate);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(SCAN_THREADS), 0, st, s.bsum, ns, p.gate);
-    hipLaunchKernelGGL(k_scan_down, dim3((unsigned)ns), dim3(SCAN_THREADS), 0, st, s.hist, L, s.bsum,
-                       p.gate);
-    const size_t lds = rs2_stage_bytes(p.n32, p.n64);
-    if (lds <= RS2_LDS_MAX) {
-        static size_t attr_set = 0;
-        if (lds > attr_set) {
-            HIP_OK(hipFuncSetAttribute((const void *)k_radix_scatter_lds,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-            attr_set = lds;
-        }
-        hipLaunchKernelGGL(k_radix_scatter_lds, dim3((unsigned)nb), dim3(RS2_THREADS), lds, st, p,
-                           (const uint32_t *)s.hist);
-    } else {
-        // a tile of this many payload words does not fit: one word per element and array
-        hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)nb), dim3(RS_THREADS), 0, st, p,
-                           (const uint32_t *)s.hist);
-    }
+    const int64_t tiles = (p.n + RS_TILE - 1) / RS_TILE;
+    const int tpb = (int)((tiles + RS_MAX_BLOCKS - 1) / RS_MAX_BLOCKS);
+    const int G = (int)((tiles + tpb - 1) / tpb);
+    hipLaunchKernelGGL(k_radix_count, dim3(G), dim3(RC_T), 0, st, p.key_in, p.n, p.shift, p.bits, tpb, s.hist,
+                       p.done, p.gate);
+    const bool iota = p.iota_slot == 0;
+    if (p.n32 == 4 && p.n64 == 0 && !iota) place_pass<4, 0, false>(p, G, tpb, s.hist, st);
+    else if (p.n32 == 1 && p.n64 == 3 && !iota) place_pass<1, 3, false>(p, G, tpb, s.hist, st);
+    else if (p.n32 == 1 && p.n64 == 0 && iota) place_pass<1, 0, true>(p, G, tpb, s.hist, st);
+    else if (p.n32 == 1 && p.n64 == 0 && !iota) place_pass<1, 0, false>(p, G, tpb, s.hist, st);
+    else return PIC_ERR_ARG;   // no caller sorts other payloads
     HIP_OK(hipGetLastError());
     return PIC_OK;
 }

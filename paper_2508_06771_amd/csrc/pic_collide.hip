@@ -687,30 +687,6 @@ __global__ __launch_bounds__(T) void k_collide(CollideArgs a, const int32_t *__r
 //     their record.
 // The pairs, the rotation (ta_half_z) and the null collisions are those of
 // cell_pass, so the two give identical velocities.
-// Workgroup barrier for LDS traffic only: waits for this wave's LDS
-// operations, not for its global loads and stores (a __syncthreads would make
-// every barrier wait for the velocity loads in flight and the stores of the
-// previous cell).  The memory clobber keeps the compiler from moving memory
-// accesses across it.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Inclusive scan of one word per lane over the wave with DPP: shifts by 1, 2,
-// 4, 8 inside each 16-lane row, then the last lane of row 0 (2) added to row
-// 1 (3) and the last lane of row 1 added to rows 2 and 3.
-__device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);   // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);   // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);   // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31
-    return x;
-}
-
 // Exclusive scan in place of the nb (a power of two) bucket counters, with
 // cnt[nb] = total.  Thread t takes the contiguous run of per = nb / T
 // counters starting at t per (one counter, or none, when nb < T): it sums
@@ -893,20 +869,6 @@ __device__ __forceinline__ void lean_round(uint32_t base, uint32_t P, uint32_t n
             vz[k] = e.z;
         }
     }
-}
-
-// Element i of a cell's array as a uniform base plus a 32-bit byte offset
-// (the scalar-base form of the global load and store): no 64-bit
-// per-member address is formed or kept live.
-template <typename X>
-__device__ __forceinline__ X ld_at(const X *base, uint32_t i)
-{
-    return *(const X *)((const char *)base + (size_t)(i * (uint32_t)sizeof(X)));
-}
-template <typename X>
-__device__ __forceinline__ void st_at(X *base, uint32_t i, X x)
-{
-    *(X *)((char *)base + (size_t)(i * (uint32_t)sizeof(X))) = x;
 }
 
 // s_waitcnt operand that waits for vector memory only: vmcnt (bits 3:0 and

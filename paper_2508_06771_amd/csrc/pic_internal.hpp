@@ -24,6 +24,7 @@ struct DevFlags {
     unsigned int count[8];  // work-queue lengths (cells per class)
     unsigned int huge_total; // members of cells in the multi-block class
     unsigned int seg_fallback; // some cell of that class takes the one-workgroup path
+    unsigned int sort_done[4];  // workgroups done counting, per re-binning pass
     unsigned int pad[5];
 };
 
@@ -410,6 +411,30 @@ __device__ __forceinline__ void block_sum_bcast(double (&x)[NV], double *red)
     __syncthreads();
 }
 
+// Workgroup barrier for LDS traffic only: waits for this wave's LDS
+// operations, not for its global loads and stores (a __syncthreads would make
+// every barrier wait for the velocity loads in flight and the stores of the
+// previous cell).  The memory clobber keeps the compiler from moving memory
+// accesses across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// Element i of an array as a uniform base plus a 32-bit byte offset
+// (the scalar-base form of the global load and store): no 64-bit
+// per-member address is formed or kept live.
+template <typename X>
+__device__ __forceinline__ X ld_at(const X *base, uint32_t i)
+{
+    return *(const X *)((const char *)base + (size_t)(i * (uint32_t)sizeof(X)));
+}
+template <typename X>
+__device__ __forceinline__ void st_at(X *base, uint32_t i, X x)
+{
+    *(X *)((char *)base + (size_t)(i * (uint32_t)sizeof(X))) = x;
+}
+
 // Inclusive scan of one uint32 per lane within a wave.
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
 {
@@ -419,6 +444,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
         uint32_t y = __shfl_up(x, o, PIC_WAVE);
         if (lane >= o) x += y;
     }
+    return x;
+}
+
+// Inclusive scan of one word per lane over the wave with DPP: shifts by 1, 2,
+// 4, 8 inside each 16-lane row, then the last lane of row 0 (2) added to row
+// 1 (3) and the last lane of row 1 added to rows 2 and 3.
+__device__ __forceinline__ uint32_t wave_incl_scan_dpp(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);   // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);   // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);   // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);   // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);   // row_bcast:31
     return x;
 }
 
@@ -704,6 +743,7 @@ struct RadixPass {
     int64_t n;
     int shift, bits;
     const int *gate;    // non-null: run only if *gate != 0
+    unsigned int *done; // zeroed counter of this pass (DevFlags::sort_done)
 };
 
 // Optional timing of selected launches with HIP events on the launch stream
@@ -719,8 +759,7 @@ bool ktime_pause();            // returns whether timing was on
 void ktime_resume(bool was);
 
 struct BinScratch {
-    uint32_t *hist;     // (1 << bits) * nblocks
-    uint32_t *bsum;     // scan block sums
+    uint32_t *hist;     // digit counts [1 << bits][workgroups], then digit starts [256]
 };
 
 size_t radix_scratch_bytes(int64_t n);
@@ -738,7 +777,6 @@ int launch_check_finite(int dtype, const void *v, int64_t n, DevFlags *flags, hi
 int launch_reject_list(DevFlags *flags, int list, hipStream_t st);
 int launch_set_step(uint64_t *step_dev, uint64_t value, hipStream_t st);
 int launch_step_inc(uint64_t *step_dev, hipStream_t st);
-int launch_copy32(uint32_t *dst, const uint32_t *src, int64_t n, const int *gate, hipStream_t st);
 
 // Work queue of cells by size class.
 struct ClassCaps {

@@ -106,38 +106,7 @@ __device__ __forceinline__ void ta_half(double ux, double uy, double uz, double 
                                         uint32_t wa3, uint32_t wb2, double &hx, double &hy,
                                         double &hz)
 {
-#pragma clang fp contract(off)
-    const double uu = ux * ux + uy * uy + uz * uz;
-    hx = hy = hz = 0.0;
-    if (uu == 0.0) return;
-    const double um = sqrt(uu);
-    const double uperp = sqrt(ux * ux + uy * uy);
-    const double z = sqrt(-2.0 * log(u01d(wa2))) * cos(2.0 * PI_D * u01d(wa3));
-    const double s2 = C / (um * um * um);
-    const double d = sqrt(s2) * z;
-    double sin_t, omc;
-    if (fabs(d) <= 1e150) {
-        sin_t = 2.0 * d / (1.0 + d * d);
-        omc = 2.0 * d * d / (1.0 + d * d);
-    } else {
-        sin_t = 2.0 / d;
-        omc = 2.0;
-    }
-    const double phi = 2.0 * PI_D * u01d(wb2);
-    const double cp = cos(phi), sp = sin(phi);
-    double dx, dy, dz;
-    if (uperp > 0.0) {
-        dx = (ux / uperp) * uz * sin_t * cp - (uy / uperp) * um * sin_t * sp - ux * omc;
-        dy = (uy / uperp) * uz * sin_t * cp + (ux / uperp) * um * sin_t * sp - uy * omc;
-        dz = -uperp * sin_t * cp - uz * omc;
-    } else {
-        dx = um * sin_t * cp;
-        dy = um * sin_t * sp;
-        dz = -uz * omc;
-    }
-    hx = 0.5 * dx;
-    hy = 0.5 * dy;
-    hz = 0.5 * dz;
+    m64_ta_half(ux, uy, uz, C, u01d(wa2), u01d(wa3), u01d(wb2), hx, hy, hz);
 }
 
 template <typename R>

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "piccoll.h"
+#include "pic_math64.hpp"
 
 #define PIC_WAVE 64
 
@@ -185,9 +186,10 @@ __device__ __forceinline__ void scatter_dir(double &vx, double &vy, double &vz, 
 {
 #pragma clang fp contract(off)
     const double ct = 1.0 - 2.0 * u01d(w.y);
-    const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
-    const double ph = 2.0 * 3.14159265358979323846 * u01d(w.z);
-    const double sx = st * cos(ph), sy = st * sin(ph), sz = ct;
+    double r, sn, cs;
+    const double st = m64_sqrt(1.0 - ct * ct, r);   // U is in (0, 1): at least 2^-22
+    m64_sincos(2.0 * 3.14159265358979323846 * u01d(w.z), sn, cs);
+    const double sx = st * cs, sy = st * sn, sz = ct;
     const double sp = sqrt(vx * vx + vy * vy + vz * vz);
     double scale = sp;
     if (mass_ratio != 0.0 && sp > 0.0) {

@@ -167,10 +167,11 @@ __device__ __forceinline__ void dsmc_dir(uint32_t wa, uint32_t wb, double &sx, d
 {
 #pragma clang fp contract(off)
     const double ct = 1.0 - 2.0 * u01d(wa);
-    const double st = sqrt(fmax(0.0, 1.0 - ct * ct));
-    const double ph = 2.0 * 3.14159265358979323846 * u01d(wb);
-    sx = st * cos(ph);
-    sy = st * sin(ph);
+    double r, sn, cs;
+    const double st = m64_sqrt(1.0 - ct * ct, r);   // U is in (0, 1): at least 2^-22
+    m64_sincos(2.0 * 3.14159265358979323846 * u01d(wb), sn, cs);
+    sx = st * cs;
+    sy = st * sn;
     sz = ct;
 }
 

@@ -30,14 +30,11 @@ __global__ void k_reset_flags(DevFlags *f)
     if (threadIdx.x == 0) {
         f->unsorted = 0;
         f->range_err = 0;
-        f->huge_total = 0;
         f->seg_fallback = 0;
         for (int k = 0; k < 4; ++k) f->sort_done[k] = 0;
     }
-    if (threadIdx.x < 8) {
-        f->head[threadIdx.x] = 0;
-        f->count[threadIdx.x] = 0;
-    }
+    if (threadIdx.x < 8) f->count[threadIdx.x] = 0;
+    for (unsigned q = threadIdx.x; q < 8 * QUEUE_SPLIT; q += blockDim.x) f->head[q * QUEUE_LINE] = 0;
 }
 
 // Any non-finite component of v latches PIC_ERR_NONFINITE (a debug check:
@@ -429,28 +426,22 @@ __global__ __launch_bounds__(RS_T) void k_radix_place(RadixPass p, int tiles_per
 }
 
 // Cells by size class.  lists[c * n_cells + k] = k-th cell of class c; the
-// class lengths go to flags->count[c]; flags->huge_total sums the members of
-// cells beyond the largest LDS class.  Within a class the order is
+// class lengths go to flags->count[c].  Within a class the order is
 // arbitrary: cells are independent and their random numbers depend only on
 // (seed, step, pid), so processing order never changes results.  Cells the
 // gate defers go to the deferred list when they still need a visit.
-// Segment plan of cell h of the multi-workgroup list with cnt members:
-// S = ceil(cnt / target) segments (equal key ranges), their table entries,
-// and the counting work items.  Segment and item ranges are reserved with atomics:
-// where a cell's entries sit never changes results.
-__device__ void plan_segments(const SegScratch &ss, DevFlags *f, int h, int32_t cnt, int target)
+// A workgroup of 1,024 cells reserves its places with one atomic per list (and
+// one for its segments and work items): these counters are contended by the
+// whole device at about 12 ns an addition, so with one addition per wave and
+// list 200,000 cells took 40 us, 16,384 cells of log-normal size 23 us.
+constexpr int QB_T = 1024;
+constexpr int QB_W = QB_T / PIC_WAVE;
+
+// Segment plan of cell h of the multi-workgroup list with cnt members: S
+// segments (equal key ranges) from table entry sb, and the counting work items
+// from cb.
+__device__ void plan_segments(const SegScratch &ss, int h, uint32_t S, uint32_t nch, uint32_t sb, uint32_t cb)
 {
-    const int64_t want = ((int64_t)cnt + target - 1) / target;
-    if (want > SEG_MAX) {
-        ss.hc_fb[h] = 1;
-        ss.hc_S[h] = 0;
-        f->seg_fallback = 1;
-        return;
-    }
-    const uint32_t S = want > 0 ? (uint32_t)want : 1u;
-    const uint32_t nch = (uint32_t)(((int64_t)cnt + SEG_CHUNK - 1) / SEG_CHUNK);
-    const uint32_t sb = atomicAdd(&f->count[SEG_SLOT], S);
-    const uint32_t cb = atomicAdd(&f->count[CHUNK_SLOT], nch);
     ss.hc_fb[h] = 0;
     ss.hc_S[h] = S;
     ss.hc_seg[h] = (int32_t)sb;
@@ -464,20 +455,21 @@ __device__ void plan_segments(const SegScratch &ss, DevFlags *f, int h, int32_t 
     for (uint32_t q = 0; q < nch; ++q) ss.ch_owner[cb + q] = h;
 }
 
-__global__ void k_build_queue(const int32_t *__restrict__ cell_start, int32_t n_cells, ClassCaps caps,
-                              int32_t *__restrict__ lists, DevFlags *f,
-                              const uint8_t *__restrict__ skip, int visit, SegScratch ss,
-                              int plan, int seg_target)
+__global__ __launch_bounds__(QB_T) void k_build_queue(const int32_t *__restrict__ cell_start, int32_t n_cells,
+                                                      ClassCaps caps, int32_t *__restrict__ lists, DevFlags *f,
+                                                      const uint8_t *__restrict__ skip, int visit,
+                                                      SegScratch ss, int plan, int seg_target)
 {
-    const int lane = threadIdx.x & (PIC_WAVE - 1);
+    __shared__ uint32_t wcnt[QUEUE_LISTS][QB_W];   // cells per list and wave, then the wave's first place
+    __shared__ uint32_t wtot[QB_W];
+    __shared__ uint32_t s_base[2];                 // first segment, first work item
+    const int lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (PIC_WAVE - lane));
-    for (int64_t j0 = blockIdx.x * (int64_t)blockDim.x; j0 < n_cells;
-         j0 += (int64_t)gridDim.x * blockDim.x) {
+    for (int64_t j0 = blockIdx.x * (int64_t)QB_T; j0 < n_cells; j0 += (int64_t)gridDim.x * QB_T) {
         const int64_t j = j0 + threadIdx.x;
-        const bool valid = j < n_cells;
         int cls = -1;
         int32_t cnt = 0;
-        if (valid) {
+        if (j < n_cells) {
             // every cell is visited: cells with fewer than two members still
             // need the null-collision step and their moment sums
             cnt = cell_start[j + 1] - cell_start[j];
@@ -486,20 +478,50 @@ __global__ void k_build_queue(const int32_t *__restrict__ cell_start, int32_t n_
                 if (cnt <= caps.cap[c]) cls = c;
             if (skip && skip[j]) cls = visit ? LIST_DEFERRED : -1;
         }
+        uint32_t mine = 0;   // place among the wave's cells of the same list
+#pragma unroll
         for (int c = 0; c < QUEUE_LISTS; ++c) {
             const uint64_t m = __ballot(cls == c);
-            if (!m) continue;
-            const int leader = __ffsll((unsigned long long)m) - 1;
-            uint32_t b = 0;
-            if (lane == leader) b = atomicAdd(&f->count[c], (uint32_t)__popcll(m));
-            b = __shfl(b, leader, PIC_WAVE);
-            if (cls == c) {
-                const int h = (int)b + __popcll(m & lt);
-                lists[(int64_t)c * n_cells + h] = (int32_t)j;
-                if (plan && c == caps.ncls) plan_segments(ss, f, h, cnt, seg_target);
+            if (cls == c) mine = (uint32_t)__popcll(m & lt);
+            if (lane == 0) wcnt[c][wid] = (uint32_t)__popcll(m);
+        }
+        __syncthreads();
+        if (threadIdx.x < QUEUE_LISTS) {
+            uint32_t tot = 0;
+            for (int w = 0; w < QB_W; ++w) tot += wcnt[threadIdx.x][w];
+            uint32_t b = tot ? atomicAdd(&f->count[threadIdx.x], tot) : 0u;
+            for (int w = 0; w < QB_W; ++w) {
+                const uint32_t c = wcnt[threadIdx.x][w];
+                wcnt[threadIdx.x][w] = b;
+                b += c;
             }
         }
-        if (cls == caps.ncls) atomicAdd(&f->huge_total, (uint32_t)cnt);
+        const bool seg = plan && cls == caps.ncls;
+        const bool any_seg = __syncthreads_or(seg ? 1 : 0) != 0;   // also: the places above are set
+        uint32_t h = 0;
+        if (cls >= 0) {
+            h = wcnt[cls][wid] + mine;
+            lists[(int64_t)cls * n_cells + h] = (int32_t)j;
+        }
+        if (any_seg) {
+            const int64_t want = ((int64_t)cnt + seg_target - 1) / seg_target;
+            const bool fb = seg && want > SEG_MAX;
+            const uint32_t S = seg && !fb ? (want > 0 ? (uint32_t)want : 1u) : 0u;
+            const uint32_t nch = S ? (uint32_t)(((int64_t)cnt + SEG_CHUNK - 1) / SEG_CHUNK) : 0u;
+            const uint32_t so = block_excl(S, wtot), co = block_excl(nch, wtot);
+            if (threadIdx.x == QB_T - 1) {
+                s_base[0] = so + S ? atomicAdd(&f->count[SEG_SLOT], so + S) : 0u;
+                s_base[1] = co + nch ? atomicAdd(&f->count[CHUNK_SLOT], co + nch) : 0u;
+            }
+            __syncthreads();
+            if (S) plan_segments(ss, (int)h, S, nch, s_base[0] + so, s_base[1] + co);
+            if (fb) {
+                ss.hc_fb[h] = 1;
+                ss.hc_S[h] = 0;
+                f->seg_fallback = 1;
+            }
+        }
+        __syncthreads();   // the shared places are rewritten by the next round
     }
 }
 
@@ -515,7 +537,7 @@ int grid_for(int64_t n, int threads, int cap)
 
 int launch_reset_flags(DevFlags *flags, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_reset_flags, dim3(1), dim3(64), 0, st, flags);
+    hipLaunchKernelGGL(k_reset_flags, dim3(1), dim3(8 * QUEUE_SPLIT), 0, st, flags);
     HIP_OK(hipGetLastError());
     return PIC_OK;
 }
@@ -605,7 +627,7 @@ int launch_build_queue(const int32_t *cell_start, int32_t n_cells, const ClassCa
     SegScratch ss;
     memset(&ss, 0, sizeof(ss));
     if (seg) ss = *seg;
-    hipLaunchKernelGGL(k_build_queue, dim3(grid_for(n_cells, 256, 1024)), dim3(256), 0, st,
+    hipLaunchKernelGGL(k_build_queue, dim3(grid_for(n_cells, QB_T, 512)), dim3(QB_T), 0, st,
                        cell_start, n_cells, caps, lists, flags, skip, visit, ss, seg ? 1 : 0,
                        seg_target);
     HIP_OK(hipGetLastError());

@@ -25,6 +25,7 @@
 // algorithm with its per-cell arrays in global scratch indexed by slot.
 #include <float.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "pic_internal.hpp"
@@ -630,13 +631,11 @@ __global__ __launch_bounds__(T) void k_collide(CollideArgs a, const int32_t *__r
     if (gated_off(a)) return;
     const uint32_t count = a.dflags->count[cls];
     if (blockIdx.x >= count) return;   // no work for this workgroup (nor a queue atomic)
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(&a.dflags->head[cls], 1u);
-        __syncthreads();
-        const int item = s_item;
-        __syncthreads();
-        if (item >= (int)count) break;
+    for (uint32_t item = blockIdx.x; item < count;) {
+        if (threadIdx.x == 0) s_item = (int)queue_take(a.dflags, cls, queue_of(blockIdx.x, gridDim.x), gridDim.x);   // read after the pass's barriers
         cell_pass<R, T, K, F>(a, list[item], smem, red, wtot, s_before);
+        item = (uint32_t)s_item;
+        __syncthreads();
     }
 }
 
@@ -971,8 +970,8 @@ __device__ __forceinline__ void lean_sort(const CollideArgs &a, int n, uint32_t 
 // sink that nothing reads): they write no register, so nothing waits for them
 // before the next cell's own loads.
 struct LeanNext {
-    int *slot;                 // LDS word receiving the next work item
-    unsigned *head;            // the queue's counter
+    int *slot;                 // LDS: [0] receives the next work item; [1] the queue, [2] the takers
+    int cls;                   // the queue
     const int32_t *list;
     uint32_t count;
     float *sink;               // 64 words of LDS
@@ -1021,7 +1020,7 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
 
     int next = 0;
     if (n == 0) {
-        if (nx && threadIdx.x == 0) *nx->slot = (int)atomicAdd(nx->head, 1u);
+        if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
         lds_barrier();   // leave together (see the end of the pass)
         if (nx) next = *nx->slot;
         lds_barrier();
@@ -1047,7 +1046,7 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
     }
     // the next work item (issued behind this cell's loads, so waiting for it
     // costs nothing extra); read after a barrier below
-    if (nx && threadIdx.x == 0) *nx->slot = (int)atomicAdd(nx->head, 1u);
+    if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
     if (n >= 2) {
         uint32_t cpid = 0;
         lean_sort<T, K, MCC, true>(a, n, step, pid_c, smem, wtot, w2, w3, key, pos, cand, cpid);
@@ -1110,15 +1109,17 @@ __global__ __launch_bounds__(T) void k_collide_lean(CollideArgs a, const int32_t
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t wtot[T / PIC_WAVE];
-    __shared__ int s_item, s_next;
+    __shared__ int s_next[3];
     __shared__ float sink[PIC_WAVE];
     if (gated_off(a)) return;
     const uint32_t count = a.dflags->count[cls];
     if (blockIdx.x >= count) return;   // no work for this workgroup (nor a queue atomic)
-    if (threadIdx.x == 0) s_item = (int)atomicAdd(&a.dflags->head[cls], 1u);
-    lds_barrier();
-    int item = s_item;
-    const LeanNext nx{&s_next, &a.dflags->head[cls], list, count, sink};
+    if (threadIdx.x == 0) {   // kept in LDS (no registers held), read by thread 0 only
+        s_next[1] = (int)queue_of(blockIdx.x, gridDim.x);
+        s_next[2] = (int)gridDim.x;
+    }
+    int item = (int)blockIdx.x;
+    const LeanNext nx{s_next, cls, list, count, sink};
     while (item < (int)count) item = lean_pass<T, K, MCC>(a, list[item], smem, wtot, &nx);
 }
 
@@ -1364,12 +1365,11 @@ __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int3
     R *vy_g = vx_g + a.n;
     R *vz_g = vy_g + a.n;
     Rec<R> *pb = (Rec<R> *)hs.pbuf;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(&a.dflags->head[cls], 1u);
+    for (uint32_t item = blockIdx.x, nxt; item < count; item = nxt) {
+        if (threadIdx.x == 0) s_item = (int)queue_take(a.dflags, cls, queue_of(blockIdx.x, gridDim.x), gridDim.x);
         __syncthreads();
-        const int item = s_item;
+        nxt = (uint32_t)s_item;
         __syncthreads();
-        if (item >= (int)count) break;
         if (only && !only[item]) continue;   // taken by the segmented path
         const int cell = list[item];
         const int lo = a.cell_start[cell];
@@ -1913,13 +1913,11 @@ __global__ __launch_bounds__(T) void k_seg_collide(CollideArgs a, const int32_t 
     if (gated_off(a)) return;
     const uint32_t count = a.dflags->count[SEG_SLOT];
     if (blockIdx.x >= count) return;   // no work for this workgroup (nor a queue atomic)
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(&a.dflags->head[SEG_SLOT], 1u);
+    for (uint32_t item = blockIdx.x; item < count;) {
+        if (threadIdx.x == 0) s_item = (int)queue_take(a.dflags, SEG_SLOT, queue_of(blockIdx.x, gridDim.x), gridDim.x);   // read after the pass's barriers
+        seg_pass<R, T, K, F>(a, list, ss, (int)item, smem, wtot);
+        item = (uint32_t)s_item;
         __syncthreads();
-        const int item = s_item;
-        __syncthreads();
-        if (item >= (int)count) break;
-        seg_pass<R, T, K, F>(a, list, ss, item, smem, wtot);
     }
 }
 
@@ -2347,12 +2345,11 @@ __global__ __launch_bounds__(1024) void k_collide_all(CollideArgs a, const int32
     const uint32_t nseg = use_seg ? a.dflags->count[SEG_SLOT] : 0u;
     const uint32_t nblk = nseg + a.dflags->pad[ORDER_TOTAL];
     const int32_t *l4 = lists + (int64_t)4 * M;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(&a.dflags->head[0], 1u);
+    for (uint32_t item = blockIdx.x, nxt; item < nblk; item = nxt) {
+        if (threadIdx.x == 0) s_item = (int)queue_take(a.dflags, 0, queue_of(blockIdx.x, gridDim.x), gridDim.x);
         lds_barrier();   // the previous cell's stores stay in flight
-        const uint32_t item = (uint32_t)s_item;
+        nxt = (uint32_t)s_item;
         lds_barrier();
-        if (item >= nblk) break;
         if (item < nseg) {
             seg_pass<R, SG::T, SG::K, F>(a, l4, ss, (int)item, smem, wtot);
             continue;
@@ -2377,12 +2374,12 @@ __global__ __launch_bounds__(1024) void k_collide_all(CollideArgs a, const int32
     const uint32_t nw = a.dflags->count[wave_cls];
     const int32_t *wl = lists + (int64_t)wave_cls * M;
     unsigned char *slice = smem + (threadIdx.x / PIC_WAVE) * WAVE_SLICE;
-    for (;;) {
-        uint32_t item = 0;
-        if ((threadIdx.x & (PIC_WAVE - 1)) == 0) item = atomicAdd(&a.dflags->head[1], 1u);
-        item = (uint32_t)__builtin_amdgcn_readfirstlane((int)__shfl(item, 0, PIC_WAVE));
-        if (item >= nw) break;
+    const uint32_t taker = blockIdx.x + gridDim.x * (threadIdx.x / PIC_WAVE);
+    const uint32_t takers = gridDim.x * (blockDim.x / PIC_WAVE);
+    for (uint32_t item = taker; item < nw;) {
         wave_pass<R, MCC>(a, wl[item], slice);
+        if ((threadIdx.x & (PIC_WAVE - 1)) == 0) item = queue_take(a.dflags, 1, queue_of(taker, takers), takers);
+        item = (uint32_t)__builtin_amdgcn_readfirstlane((int)item);
     }
 }
 
@@ -2398,7 +2395,7 @@ int launch_class(const CollideArgs &a, const int32_t *list, int cls, int blocks,
         attr_done = true;
     }
     ktime_begin(KT_CLASS0 + cls, st);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(T), lds, st, a, list, cls);
+    hipLaunchKernelGGL(kern, dim3(persistent_grid(blocks)), dim3(T), lds, st, a, list, cls);
     ktime_end(KT_CLASS0 + cls, st);
     HIP_OK(hipGetLastError());
     return PIC_OK;
@@ -2420,7 +2417,7 @@ int launch_class_best(const CollideArgs &a, const int32_t *list, int cls, int bl
             attr_done = true;
         }
         ktime_begin(KT_CLASS0 + cls, st);
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(T), lds, st, a, list, cls);
+        hipLaunchKernelGGL(kern, dim3(persistent_grid(blocks)), dim3(T), lds, st, a, list, cls);
         ktime_end(KT_CLASS0 + cls, st);
         HIP_OK(hipGetLastError());
         return PIC_OK;
@@ -2461,7 +2458,7 @@ int launch_seg_collide(const CollideArgs &a, const int32_t *list, const SegScrat
                                    (int)lds));
         attr_done = true;
     }
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(T), lds, st, a, list, ss);
+    hipLaunchKernelGGL(kern, dim3(persistent_grid(blocks)), dim3(T), lds, st, a, list, ss);
     HIP_OK(hipGetLastError());
     return PIC_OK;
 }
@@ -2478,9 +2475,18 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
     const int64_t M = n_cells;
     const int *bp = caps.blocks_per_cu;
     const int32_t *l4 = lists + 4 * M;
+    // A list's cells have more members than the class below takes, so the
+    // n members fill at most n / (cap + 1) of them: no more workgroups than
+    // that, and no launch for a list that cannot hold a cell.  The binary64 lean
+    // passes take one workgroup per cell: with one for each cell of the grid
+    // their empty launches cost 40 us each on 40,000 small cells.
+    auto most = [&](int c) { return c == 0 ? M : std::min(M, a.n / ((int64_t)caps.cap[c - 1] + 1)); };
+    auto grid = [&](int c) { return (int)std::min<int64_t>(bp[c] * num_cu, most(c)); };
+    for (int c = 1; c <= 4; ++c)
+        if (most(c) == 0) live &= ~(1u << c);
     // largest cells first so the small ones fill the tail
-    ktime_begin(KT_HUGE, st);
     bool seg_done = !(live & (1u << 4));   // no cell beyond the LDS classes
+    if (!seg_done) ktime_begin(KT_HUGE, st);
     if constexpr (SEG_OK) {
       if (!seg_done && seg_path) {
         seg_done = true;
@@ -2493,14 +2499,14 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
         if ((rc = launch_seg_collide<R, G::T, G::K, F>(a, l4, ss, G::PER_CU * num_cu, st))) return rc;
         hipLaunchKernelGGL(k_seg_fixup<R>, dim3(num_cu), dim3(256), 0, st, a, l4, ss);
         // cells the plan could not segment
-        hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(num_cu * bp[4]), dim3(1024), 0, st, a, l4, 4,
+        hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
                            hs, (const uint8_t *)ss.hc_fb);
       }
     }
     if (!seg_done)
-        hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(num_cu * bp[4]), dim3(1024), 0, st, a, l4, 4,
+        hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
                            hs, (const uint8_t *)nullptr);
-    ktime_end(KT_HUGE, st);
+    if (live & (1u << 4)) ktime_end(KT_HUGE, st);
     HIP_OK(hipGetLastError());
     if (live & (1u << 3)) {
         // binary64 plain steps whose caps widen the largest class: the lean pass
@@ -2508,33 +2514,29 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
         if constexpr (std::is_same<R, double>::value && (F & ~F_MCC) == 0) {
             if (caps.cap[3] > C::T3 * C::K3) {
                 // one workgroup per listed cell (the kernel is not persistent)
-                if ((rc = launch_lean64<(F & F_MCC) != 0>(a, lists + 3 * M, 3, (int)M, st)))
+                if ((rc = launch_lean64<(F & F_MCC) != 0>(a, lists + 3 * M, 3, (int)most(3), st)))
                     return rc;
                 done = true;
             }
         }
-        if (!done &&
-            (rc = launch_class_best<R, C::T3, C::K3, F>(a, lists + 3 * M, 3, bp[3] * num_cu, st)))
+        if (!done && (rc = launch_class_best<R, C::T3, C::K3, F>(a, lists + 3 * M, 3, grid(3), st)))
             return rc;
     }
     if (live & (1u << 2)) {
         bool done = false;
         if constexpr (std::is_same<R, double>::value && (F & ~F_MCC) == 0) {
             if (caps.cap[3] > C::T3 * C::K3) {   // the binary64 plain step's lean passes
-                if ((rc = launch_lean64<(F & F_MCC) != 0, C::K2>(a, lists + 2 * M, 2, (int)M, st)))
+                if ((rc = launch_lean64<(F & F_MCC) != 0, C::K2>(a, lists + 2 * M, 2, (int)most(2), st)))
                     return rc;
                 done = true;
             }
         }
-        if (!done &&
-            (rc = launch_class_best<R, C::T2, C::K2, F>(a, lists + 2 * M, 2, bp[2] * num_cu, st)))
+        if (!done && (rc = launch_class_best<R, C::T2, C::K2, F>(a, lists + 2 * M, 2, grid(2), st)))
             return rc;
     }
-    if ((live & (1u << 1)) &&
-        (rc = launch_class_best<R, C::T1, C::K1, F>(a, lists + 1 * M, 1, bp[1] * num_cu, st)))
+    if ((live & (1u << 1)) && (rc = launch_class_best<R, C::T1, C::K1, F>(a, lists + 1 * M, 1, grid(1), st)))
         return rc;
-    if ((live & (1u << 0)) &&
-        (rc = launch_class<R, C::T0, C::K0, F>(a, lists + 0 * M, 0, bp[0] * num_cu, st)))
+    if ((live & (1u << 0)) && (rc = launch_class<R, C::T0, C::K0, F>(a, lists + 0 * M, 0, grid(0), st)))
         return rc;
     return PIC_OK;
 }
@@ -2590,17 +2592,17 @@ int launch_unified(const CollideArgs &a, const int32_t *lists, int32_t n_cells, 
         attr_done = true;
     }
     ktime_begin(KT_ALL, st);
-    hipLaunchKernelGGL(kern, dim3(num_cu), dim3(1024), lds, st, a, lists, n_cells,
+    hipLaunchKernelGGL(kern, dim3(persistent_grid(num_cu)), dim3(1024), lds, st, a, lists, n_cells,
                        (const int32_t *)a.order, ss, caps, seg_path ? 1 : 0, wave_cls);
     ktime_end(KT_ALL, st);
     HIP_OK(hipGetLastError());
     ktime_begin(KT_HUGE, st);
     if (seg_path) {
         hipLaunchKernelGGL(k_seg_fixup<R>, dim3(num_cu), dim3(256), 0, st, a, l4, ss);
-        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(num_cu), dim3(1024), 0, st, a, l4, 4, hs,
+        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs,
                            (const uint8_t *)ss.hc_fb);
     } else {
-        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(num_cu), dim3(1024), 0, st, a, l4, 4, hs,
+        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs,
                            (const uint8_t *)nullptr);
     }
     ktime_end(KT_HUGE, st);

@@ -322,6 +322,83 @@ __device__ __forceinline__ void cell_moments_out(double *out, const R (&vx)[K], 
     __syncthreads();
 }
 
+// Adds the thread's members to s: sum v, sum |v|^2.
+template <typename R, int T, int K>
+__device__ __forceinline__ void add_sums(double *s, int n, const R (&vx)[K], const R (&vy)[K], const R (&vz)[K])
+{
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int i = threadIdx.x + k * T;
+        if (i < n) {
+            const double x = vx[k], y = vy[k], z = vz[k];
+            s[0] += x;
+            s[1] += y;
+            s[2] += z;
+            s[3] += x * x + y * y + z * z;
+        }
+    }
+}
+
+// The conservation correction of a cell of n members whose velocities sit in
+// registers: before and after are its sums around the step, debt (four
+// doubles, nullable) what earlier steps left unmet; what the output rounding
+// leaves goes to debt_out (nullable).  Contains barriers.
+template <typename R, int T, int K>
+__device__ __forceinline__ void conserve_regs(int n, R (&vx)[K], R (&vy)[K], R (&vz)[K], const double *before,
+                                              const double *after, const double *debt, double *debt_out,
+                                              double *red)
+{
+    const Correction cr = make_correction((double)n, before, after, debt);
+    if (cr.ok) {
+        double real[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int i = threadIdx.x + k * T;
+            if (i < n) {
+                vx[k] = (R)(cr.Vt[0] + cr.al * ((double)vx[k] - cr.Vn[0]));
+                vy[k] = (R)(cr.Vt[1] + cr.al * ((double)vy[k] - cr.Vn[1]));
+                vz[k] = (R)(cr.Vt[2] + cr.al * ((double)vz[k] - cr.Vn[2]));
+            }
+        }
+        add_sums<R, T, K>(real, n, vx, vy, vz);
+        const double t = block_sum_scatter<4>(real, red);
+        if (debt_out) store_debt_lane(debt_out, cr, t);
+    }
+}
+
+// Null collisions of the thread's candidate members (bits of cand) on their
+// registers, one candidate at a time per lane.
+template <typename R, int T, int K>
+__device__ __forceinline__ void scatter_regs(const CollideArgs &a, uint32_t cand, R (&vx)[K], R (&vy)[K],
+                                             R (&vz)[K], const uint32_t *pid_c, uint32_t step)
+{
+    uint32_t left = cand;
+    while (__ballot(left != 0u) != 0ull) {
+        if (left) {
+            const int kk = __builtin_ctz(left);
+            left &= left - 1u;
+            // selected and put back without a branch (a conditional access is
+            // turned into an indexed one, and the arrays into scratch memory)
+            R x = vx[0], y = vy[0], z = vz[0];
+#pragma unroll
+            for (int k = 1; k < K; ++k) {
+                const R ax = vx[k], ay = vy[k], az = vz[k];
+                x = kk == k ? ax : x;
+                y = kk == k ? ay : y;
+                z = kk == k ? az : z;
+            }
+            mcc_scatter<R>(x, y, z, pid_c[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const R ax = vx[k], ay = vy[k], az = vz[k];
+                vx[k] = kk == k ? x : ax;
+                vy[k] = kk == k ? y : ay;
+                vz[k] = kk == k ? z : az;
+            }
+        }
+    }
+}
+
 template <typename R, int T, int K, int F>
 __device__ __forceinline__ void cell_pass(const CollideArgs &a, int cell, unsigned char *smem, double *red,
                           uint32_t *wtot, double *s_before)
@@ -538,39 +615,10 @@ __device__ __forceinline__ void cell_pass(const CollideArgs &a, int cell, unsign
 
         if constexpr (CONS) {
             double after[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int i = threadIdx.x + k * T;
-                if (i < n) {
-                    const double x = vx[k], y = vy[k], z = vz[k];
-                    after[0] += x;
-                    after[1] += y;
-                    after[2] += z;
-                    after[3] += x * x + y * y + z * z;
-                }
-            }
+            add_sums<R, T, K>(after, n, vx, vy, vz);
             block_sum_bcast<4>(after, red);
-            const Correction cr = make_correction((double)n, s_before, after,
-                                                  a.debt ? a.debt + (int64_t)cell * 4 : nullptr);
-            if (cr.ok) {
-                double real[4] = {0, 0, 0, 0};
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const int i = threadIdx.x + k * T;
-                    if (i < n) {
-                        vx[k] = (R)(cr.Vt[0] + cr.al * ((double)vx[k] - cr.Vn[0]));
-                        vy[k] = (R)(cr.Vt[1] + cr.al * ((double)vy[k] - cr.Vn[1]));
-                        vz[k] = (R)(cr.Vt[2] + cr.al * ((double)vz[k] - cr.Vn[2]));
-                        const double x = vx[k], y = vy[k], z = vz[k];
-                        real[0] += x;
-                        real[1] += y;
-                        real[2] += z;
-                        real[3] += x * x + y * y + z * z;
-                    }
-                }
-                const double t = block_sum_scatter<4>(real, red);
-                if (a.debt) store_debt_lane(a.debt + (int64_t)cell * 4, cr, t);
-            }
+            double *debt = a.debt ? a.debt + (int64_t)cell * 4 : nullptr;
+            conserve_regs<R, T, K>(n, vx, vy, vz, s_before, after, debt, debt, red);
         }
     }
 
@@ -578,31 +626,7 @@ __device__ __forceinline__ void cell_pass(const CollideArgs &a, int cell, unsign
     // takes its candidates one at a time (selected out of its register slots)
     // instead of branching per slot, which would run the scattering for every
     // slot holding a candidate in any lane of the wave
-    if constexpr (MCC) {
-        uint32_t left = cand;
-        while (__ballot(left != 0u) != 0ull) {
-            if (left) {
-                const int kk = __builtin_ctz(left);
-                left &= left - 1u;
-                R x = vx[0], y = vy[0], z = vz[0];
-#pragma unroll
-                for (int k = 1; k < K; ++k)
-                    if (kk == k) {
-                        x = vx[k];
-                        y = vy[k];
-                        z = vz[k];
-                    }
-                mcc_scatter<R>(x, y, z, pid_c[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
-#pragma unroll
-                for (int k = 0; k < K; ++k)
-                    if (kk == k) {
-                        vx[k] = x;
-                        vy[k] = y;
-                        vz[k] = z;
-                    }
-            }
-        }
-    }
+    if constexpr (MCC) scatter_regs<R, T, K>(a, cand, vx, vy, vz, pid_c, step);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = threadIdx.x + k * T;
@@ -640,8 +664,7 @@ __global__ __launch_bounds__(T) void k_collide(CollideArgs a, const int32_t *__r
 }
 
 // ------------------------------------------------------------ lean pass
-// The binary32 pass of the plain step (optionally with the fused null
-// collisions) for cells of up to T*K members, written for few VALU
+// The binary32 pass for cells of up to T*K members, written for few VALU
 // instructions and few LDS operations per member:
 //   * bucket counters are whole words (no 16-bit packing), nb = 2^bits >= n
 //     buckets, so a bucket holds 0.5..1 members on average;
@@ -650,7 +673,7 @@ __global__ __launch_bounds__(T) void k_collide(CollideArgs a, const int32_t *__r
 //     (about half the members are alone in their bucket);
 //   * the first member of each pair draws its Box-Muller deviate before the
 //     exchange, so a record is 16 bytes (velocity and one word) and a cell of
-//     up to lean_positions(T*K) members exchanges in one round;
+//     up to LeanExch::P members exchanges in one round;
 //   * pair threads write both new velocities back in place; members read
 //     their record.
 // The pairs, the rotation (ta_half_z) and the null collisions are those of
@@ -729,67 +752,155 @@ struct LeanGeom {
     static constexpr size_t SORT_BYTES = CNT_WORDS * 4 + ((size_t)CAP + 4) * 4 + (size_t)CAP * 2;
 };
 
-// Dynamic LDS the lean pass may use (its static part is below 512 bytes).
+// Dynamic LDS the lean passes may use: a whole CU's for the 1,024-thread ones
+// (their static part is below 512 bytes, with the cell's sums below 3 KB), half
+// of it for the 512-thread ones, so that two workgroups fit on a CU.
 constexpr size_t LEAN_LDS_LIMIT = 160 * 1024 - 512;
 
-// Positions exchanged per round: the whole cell when its records fit.
-__host__ __device__ constexpr uint32_t lean_positions(int cap)
-{
-    const size_t want = ((size_t)cap + 1) & ~(size_t)1;
-    const size_t lim = (LEAN_LDS_LIMIT / sizeof(Rec<float>)) & ~(size_t)63;
-    return (uint32_t)(want < lim ? want : lim);
-}
+// One exchange round over P sorted positions: a record each; with weights the
+// weight per position and the second members' word 3 per pair, with Nanbu's
+// operator or the triplet the member index per position (the triplet may need
+// two positions past the round).  P covers the whole cell where that fits.
+template <int T, int K, int F>
+struct LeanExch {
+    static constexpr bool WT = (F & F_WT) != 0;
+    static constexpr bool SLOT = (F & (F_NANBU | F_TRIP)) != 0;
+    static constexpr uint32_t EXTRA = (F & F_TRIP) ? 2u : 0u;
+    static constexpr size_t LIMIT = T >= 1024 ? LEAN_LDS_LIMIT - ((F & (F_CONS | F_MOM)) ? 2560 : 0)
+                                              : 80 * 1024 - ((F & (F_CONS | F_MOM)) ? 2048 : 512);
+    static constexpr size_t bytes(uint32_t P)
+    {
+        size_t b = ((size_t)P + EXTRA) * sizeof(Rec<float>);
+        if (WT) b += (size_t)P * 4 + (size_t)P / 2 * 4;
+        if (SLOT) b += ((size_t)P + EXTRA) * 2;
+        return (b + 15) & ~(size_t)15;
+    }
+    static constexpr uint32_t fit()
+    {
+        const uint32_t want = ((uint32_t)(T * K) + 1u) & ~1u;
+        uint32_t P = (want + 63u) & ~63u;
+        while (P > 64 && bytes(P) > LIMIT) P -= 64;
+        return P < want ? P : want;
+    }
+    static constexpr uint32_t P = fit();
+};
 
-template <int T, int K>
+template <int T, int K, int F>
 __host__ __device__ constexpr size_t lean_lds_bytes()
 {
-    const size_t ex = (size_t)lean_positions(T * K) * sizeof(Rec<float>);
+    const size_t ex = LeanExch<T, K, F>::bytes(LeanExch<T, K, F>::P);
     const size_t s = LeanGeom<T, K>::SORT_BYTES;
     return s > ex ? s : ex;
 }
 
 // One exchange round over the sorted positions [base, base + P): members post
 // (velocity, word) at their position (the unpaired last one too), one thread
-// per pair rotates, null-collision candidates scatter their records, members
+// per pair rotates, null-collision candidates scatter their records (with the
+// conservation correction, which comes first, they wait for lean_pass), members
 // read their record back.  Contains the barriers.
-template <int T, int K, bool MCC>
-__device__ __forceinline__ void lean_round(uint32_t base, uint32_t P, uint32_t np2, int n, float C,
-                                           Rec<float> *rec, float (&vx)[K], float (&vy)[K],
-                                           float (&vz)[K], const uint32_t (&w2)[K],
-                                           const uint32_t (&w3)[K], const uint32_t (&pos)[K],
-                                           uint32_t &cand, int kf, uint32_t cpid,
-                                           const uint32_t *pid_c, const CollideArgs &a,
-                                           uint32_t step)
+template <int T, int K, int F>
+__device__ __forceinline__ void lean_round(uint32_t base, uint32_t np2, int n, float C, unsigned char *smem,
+                                           float (&vx)[K], float (&vy)[K], float (&vz)[K],
+                                           const uint32_t (&w2)[K], const uint32_t (&w3)[K],
+                                           const float (&wt)[(F & F_WT) ? K : 1], const uint32_t (&pos)[K],
+                                           uint32_t &cand, int kf, uint32_t cpid, const uint32_t *pid_c,
+                                           const CollideArgs &a, int cell, uint32_t step)
 {
+    typedef LeanExch<T, K, F> X;
+    constexpr bool MCC = (F & F_MCC) != 0 && (F & F_CONS) == 0;
+    constexpr bool WT = (F & F_WT) != 0, NANBU = (F & F_NANBU) != 0, TRIP = (F & F_TRIP) != 0;
+    constexpr uint32_t P = X::P;
+    Rec<float> *rec = (Rec<float> *)smem;
+    float *wts = (float *)(rec + P + X::EXTRA);
+    uint32_t *w3b = (uint32_t *)(wts + (WT ? P : 0));
+    uint16_t *slt = (uint16_t *)(w3b + (WT ? P / 2 : 0));
+    // with the triplet, an odd cell's last three positions form it, in the
+    // round that holds its start
+    const uint32_t tstart = (TRIP && (n & 1) && n >= 3) ? (uint32_t)n - 3u : np2;
+    const bool tri_here = TRIP && tstart < np2 && tstart - base < P;
+    auto mine = [&](uint32_t p) { return (!TRIP || tstart == np2 || p < tstart) ? p - base < P : tri_here; };
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = threadIdx.x + k * T;
         const uint32_t q = pos[k] - base;
-        if (i < n && q < P) {
-            // first members carry their deviate, second ones word 2
-            const float z = ta_z(w2[k], w3[k]);
+        if (i < n && mine(pos[k])) {
             Rec<float> e;
             e.x = vx[k];
             e.y = vy[k];
             e.z = vz[k];
-            e.w2 = (pos[k] & 1u) ? w2[k] : __float_as_uint(z);
+            if constexpr (NANBU) {
+                e.w2 = w2[k];
+            } else {
+                // first members carry their deviate, second ones word 2
+                const float z = ta_z(w2[k], w3[k]);
+                e.w2 = (pos[k] & 1u) ? w2[k] : __float_as_uint(z);
+            }
             rec[q] = e;
+            if constexpr (WT) {
+                wts[q] = wt[k];
+                if (q & 1u) w3b[q >> 1] = w3[k];
+            }
+            if constexpr (X::SLOT) slt[q] = (uint16_t)i;
         }
     }
     lds_barrier();
-    const uint32_t m = min(P, np2 - base) / 2;
+    const uint32_t lim = min(base + P, tstart);
+    const uint32_t m = lim > base ? (lim - base) / 2 : 0u;
     for (uint32_t j = threadIdx.x; j < m; j += T) {
         Rec<float> A = rec[2 * j], B = rec[2 * j + 1];
         float hx, hy, hz;
-        ta_half_z(A.x - B.x, A.y - B.y, A.z - B.z, C, __uint_as_float(A.w2), B.w2, hx, hy, hz);
-        A.x += hx;
-        A.y += hy;
-        A.z += hz;
-        B.x -= hx;
-        B.y -= hy;
-        B.z -= hz;
+        bool ta = true, tb = true;
+        if constexpr (NANBU) {
+            // the member in the lower storage slot is the operator's first
+            if (slt[2 * j] < slt[2 * j + 1]) {
+                nanbu_half<float>(A.x - B.x, A.y - B.y, A.z - B.z, C, A.w2, B.w2, hx, hy, hz);
+            } else {
+                nanbu_half<float>(B.x - A.x, B.y - A.y, B.z - A.z, C, B.w2, A.w2, hx, hy, hz);
+                hx = -hx;
+                hy = -hy;
+                hz = -hz;
+            }
+        } else {
+            ta_half_z(A.x - B.x, A.y - B.y, A.z - B.z, C, __uint_as_float(A.w2), B.w2, hx, hy, hz);
+            if constexpr (WT) weight_rule<float>(wts[2 * j], wts[2 * j + 1], w3b[j], ta, tb);
+        }
+        if (ta) {
+            A.x += hx;
+            A.y += hy;
+            A.z += hz;
+        }
+        if (tb) {
+            B.x -= hx;
+            B.y -= hy;
+            B.z -= hz;
+        }
         rec[2 * j] = A;
         rec[2 * j + 1] = B;
+    }
+    if constexpr (TRIP) {
+        if (tri_here && threadIdx.x == 0) {
+            const uint32_t q0 = tstart - base;
+            float x[3], y[3], z[3];
+            uint32_t pd[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const Rec<float> e = rec[q0 + c];
+                x[c] = e.x;
+                y[c] = e.y;
+                z[c] = e.z;
+                pd[c] = pid_c[slt[q0 + c]];
+            }
+            const double dens = a.density ? a.density[cell] : 1.0;
+            triplet_collide<float>(x, y, z, pd, (float)(8.0 * PI_D * dens * a.lnL * (0.5 * a.dt)), a.seed, step);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                Rec<float> e = rec[q0 + c];
+                e.x = x[c];
+                e.y = y[c];
+                e.z = z[c];
+                rec[q0 + c] = e;
+            }
+        }
     }
     lds_barrier();
     // null collisions of this round's candidates, on their own records (each
@@ -830,7 +941,7 @@ __device__ __forceinline__ void lean_round(uint32_t base, uint32_t P, uint32_t n
     for (int k = 0; k < K; ++k) {
         const int i = threadIdx.x + k * T;
         const uint32_t q = pos[k] - base;
-        if (i < n && q < P) {
+        if (i < n && mine(pos[k])) {
             const Rec<float> e = rec[q];
             vx[k] = e.x;
             vy[k] = e.y;
@@ -1000,12 +1111,14 @@ __device__ __forceinline__ void prefetch_cell(const CollideArgs &a, int cell, fl
 // returns it (every thread reads it after a barrier that follows its write
 // and precedes the pass's end, so the next pass may overwrite the slot);
 // without, it returns 0.
-template <int T, int K, bool MCC>
+template <int T, int K, int F>
 __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigned char *smem, uint32_t *wtot,
-                                         const LeanNext *nx = nullptr)
+                                         const LeanNext *nx = nullptr, double *red = nullptr,
+                                         double *s_debt = nullptr)
 {
-    typedef LeanGeom<T, K> G;
-    constexpr uint32_t P = lean_positions(G::CAP);
+    constexpr bool MCC = (F & F_MCC) != 0, CONS = (F & F_CONS) != 0, MOM = (F & F_MOM) != 0;
+    constexpr bool WT = (F & F_WT) != 0;
+    constexpr uint32_t P = LeanExch<T, K, F>::P;
     const int lo = a.cell_start[cell];
     const int n = a.cell_start[cell + 1] - lo;
     const uint32_t step = (uint32_t)read_step(a);
@@ -1015,11 +1128,14 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
     const uint32_t *pid_c = a.pid + lo;
 
     float vx[K], vy[K], vz[K];
+    float wt[WT ? K : 1];
     uint32_t w2[K], w3[K], key[K], pos[K];
     uint32_t cand = 0;
 
     int next = 0;
     if (n == 0) {
+        if constexpr (MOM)
+            if (threadIdx.x < 14) a.moments[(int64_t)cell * 14 + threadIdx.x] = 0.0;
         if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
         lds_barrier();   // leave together (see the end of the pass)
         if (nx) next = *nx->slot;
@@ -1043,7 +1159,14 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
             vy[k] = ld_at((const float *)vy_g, ic[k]);
             vz[k] = ld_at((const float *)vz_g, ic[k]);
         }
+        if constexpr (WT && T < 1024) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) wt[k] = ld_at((const float *)a.w + lo, ic[k]);
+        }
     }
+    // the cell's shortfall, read behind the other loads (and barriers later)
+    if constexpr (CONS)
+        if (a.debt && threadIdx.x < 4) s_debt[threadIdx.x] = a.debt[(int64_t)cell * 4 + threadIdx.x];
     // the next work item (issued behind this cell's loads, so waiting for it
     // costs nothing extra); read after a barrier below
     if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
@@ -1051,6 +1174,15 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
         uint32_t cpid = 0;
         lean_sort<T, K, MCC, true>(a, n, step, pid_c, smem, wtot, w2, w3, key, pos, cand, cpid);
         lds_barrier();   // the sort's memory becomes the exchange records
+        if constexpr (WT && T >= 1024) {   // only now: the sort has no registers to spare
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                wt[k] = ld_at((const float *)a.w + lo, (uint32_t)min((int)threadIdx.x + k * T, n - 1));
+        }
+        // the thread's part of the sums before the step waits in registers for
+        // the sums after it: one reduction of eight values for both
+        double sums[CONS ? 8 : 1] = {0};
+        if constexpr (CONS) add_sums<float, T, K>(sums, n, vx, vy, vz);
 
         const float C = (float)cell_C(a, cell);
         // last global loads before the exchange: a later wait for a load (the
@@ -1061,12 +1193,21 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
             if (nxt < nx->count) prefetch_cell<T>(a, nx->list[nxt], nx->sink);
         }
         const uint32_t np2 = (uint32_t)n & ~1u;     // positions with a partner
-        Rec<float> *rec = (Rec<float> *)smem;
         const int kf = cand ? __builtin_ctz(cand) : K;
         for (uint32_t base = 0; base < (uint32_t)n; base += P) {
             if (base) lds_barrier();
-            lean_round<T, K, MCC>(base, P, np2, opaque(n), C, rec, vx, vy, vz, w2, w3, pos, cand,
-                                  kf, cpid, pid_c, a, step);
+            lean_round<T, K, F>(base, np2, opaque(n), C, smem, vx, vy, vz, w2, w3, wt, pos, cand, kf, cpid, pid_c,
+                                a, cell, step);
+        }
+        if constexpr (CONS) {
+            add_sums<float, T, K>(sums + 4, n, vx, vy, vz);
+            block_sum_bcast<8>(sums, red);
+            conserve_regs<float, T, K>(n, vx, vy, vz, sums, sums + 4, a.debt ? s_debt : nullptr,
+                                       a.debt ? a.debt + (int64_t)cell * 4 : nullptr, red);
+            if constexpr (MCC) {
+                scatter_regs<float, T, K>(a, cand, vx, vy, vz, pid_c, step);
+                cand = 0;
+            }
         }
     } else if (MCC) {
         const W4 w = draw4(a.seed, pos[0], step, 0u, 0u);
@@ -1091,6 +1232,7 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
             vz_g[i] = vz[k];
         }
     }
+    if constexpr (MOM) cell_moments_out<float, T, K>(a.moments + (int64_t)cell * 14, vx, vy, vz, n, red);
     // the next item: written by thread 0 before at least one barrier of
     // this pass when n >= 2 (else one more barrier), read by everyone before
     // the last one (the next pass writes it only after that)
@@ -1103,7 +1245,7 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
     return next;
 }
 
-template <int T, int K, bool MCC>
+template <int T, int K, int F>
 __global__ __launch_bounds__(T) void k_collide_lean(CollideArgs a, const int32_t *__restrict__ list,
                                                     int cls)
 {
@@ -1120,7 +1262,13 @@ __global__ __launch_bounds__(T) void k_collide_lean(CollideArgs a, const int32_t
     }
     int item = (int)blockIdx.x;
     const LeanNext nx{s_next, cls, list, count, sink};
-    while (item < (int)count) item = lean_pass<T, K, MCC>(a, list[item], smem, wtot, &nx);
+    if constexpr ((F & (F_CONS | F_MOM)) != 0) {
+        __shared__ double red[16 * (T / PIC_WAVE)];
+        __shared__ double s_debt[4];
+        while (item < (int)count) item = lean_pass<T, K, F>(a, list[item], smem, wtot, &nx, red, s_debt);
+    } else {
+        while (item < (int)count) item = lean_pass<T, K, F>(a, list[item], smem, wtot, &nx);
+    }
 }
 
 // ------------------------------------------------------------ lean pass, binary64
@@ -2360,7 +2508,7 @@ __global__ __launch_bounds__(1024) void k_collide_all(CollideArgs a, const int32
             // one geometry for every block cell (a second one in the same
             // kernel pushes the largest past the register file)
             (void)n;
-            lean_pass<1024, CL::K3, MCC>(a, cell, smem, wtot);
+            lean_pass<1024, CL::K3, F>(a, cell, smem, wtot);
         } else {
             __shared__ double red[16 * 16];
             __shared__ double s_before[4];
@@ -2401,15 +2549,14 @@ int launch_class(const CollideArgs &a, const int32_t *list, int cls, int blocks,
     return PIC_OK;
 }
 
-// The lean pass for binary32 steps without conservation sums, moment sums or
-// the pairing export; cell_pass otherwise.
+// The lean pass for binary32 steps (all but the pairing export); cell_pass
+// otherwise.
 template <typename R, int T, int K, int F>
 int launch_class_best(const CollideArgs &a, const int32_t *list, int cls, int blocks, hipStream_t st)
 {
-    if constexpr (std::is_same<R, float>::value && (F & ~F_MCC) == 0) {
-        constexpr bool MCC = (F & F_MCC) != 0;
-        const size_t lds = lean_lds_bytes<T, K>();
-        auto kern = k_collide_lean<T, K, MCC>;
+    if constexpr (std::is_same<R, float>::value && (F & F_PAIRS) == 0) {
+        const size_t lds = lean_lds_bytes<T, K, F>();
+        auto kern = k_collide_lean<T, K, F>;
         static bool attr_done = false;
         if (!attr_done) {
             HIP_OK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -2551,7 +2698,7 @@ constexpr size_t all_lds_bytes()
     const size_t seg = lds_bytes<R>(SegGeom<R>::T * SegGeom<R>::K);
     b = seg > b ? seg : b;
     if constexpr (std::is_same<R, float>::value && (F & ~F_MCC) == 0) {
-        const size_t l = lean_lds_bytes<1024, CL::K3>();
+        const size_t l = lean_lds_bytes<1024, CL::K3, F>();
         b = l > b ? l : b;
     } else {
         const size_t l = lds_bytes<R>(1024 * CL::K3);

@@ -261,9 +261,12 @@ __device__ __forceinline__ Correction make_correction(double N, const double *b,
         c.Q += debt[3];
     }
     double vt2 = 0.0, vn2 = 0.0;
+    // six quotients by N from one reciprocal (every thread of a cell computes
+    // them: six library divisions were as much work as the cell's sums)
+    const double r = m64_rcp(N);
     for (int a = 0; a < 3; ++a) {
-        c.Vt[a] = c.P[a] / N;
-        c.Vn[a] = f[a] / N;
+        c.Vt[a] = m64_div(c.P[a], N, r);
+        c.Vn[a] = m64_div(f[a], N, r);
         vt2 += c.Vt[a] * c.Vt[a];
         vn2 += c.Vn[a] * c.Vn[a];
     }
@@ -290,6 +293,16 @@ __device__ __forceinline__ void store_debt_lane(double *debt, const Correction &
 {
     const unsigned t = threadIdx.x;
     if (t < 4) debt[t] = (t == 0 ? c.P[0] : t == 1 ? c.P[1] : t == 2 ? c.P[2] : c.Q) - real_t;
+}
+
+// Workgroup barrier for LDS traffic only: waits for this wave's LDS
+// operations, not for its global loads and stores (a __syncthreads would make
+// every barrier wait for the velocity loads in flight and the stores of the
+// previous cell).  The memory clobber keeps the compiler from moving memory
+// accesses across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // ---------------------------------------------------------------------------
@@ -408,49 +421,41 @@ __device__ __forceinline__ void wave_scatter_to(double (&x)[NV], double *red)
 
 // Block totals of NV doubles: thread t < NV returns the total of value t
 // (waves added in order), other threads 0.  red: NV * (blockDim / 64)
-// doubles of LDS.  Contains the barriers (red is free again on return).
+// doubles of LDS.  Contains the barriers (LDS only; red is
+// free again on return).
 template <int NV>
 __device__ __forceinline__ double block_sum_scatter(double (&x)[NV], double *red)
 {
     wave_scatter_to<NV>(x, red);
-    __syncthreads();
+    lds_barrier();
     double s = 0.0;
     if (threadIdx.x < NV) {
         const int nw = blockDim.x / PIC_WAVE;
         for (int w = 0; w < nw; ++w) s += red[w * NV + threadIdx.x];
     }
-    __syncthreads();
+    lds_barrier();
     return s;
 }
 
 // Block totals of NV doubles, returned to every thread in x.  red:
-// NV * (blockDim / 64 + 1) doubles of LDS.  Contains the barriers.
+// NV * (blockDim / 64 + 1) doubles of LDS.  Contains the barriers (LDS only).
 template <int NV>
 __device__ __forceinline__ void block_sum_bcast(double (&x)[NV], double *red)
 {
     const int nw = blockDim.x / PIC_WAVE;
     wave_scatter_to<NV>(x, red);
-    __syncthreads();
+    lds_barrier();
     if (threadIdx.x < NV) {
         double s = 0.0;
         for (int w = 0; w < nw; ++w) s += red[w * NV + threadIdx.x];
         red[nw * NV + threadIdx.x] = s;
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int j = 0; j < NV; ++j) x[j] = red[nw * NV + j];
-    __syncthreads();
+    lds_barrier();
 }
 
-// Workgroup barrier for LDS traffic only: waits for this wave's LDS
-// operations, not for its global loads and stores (a __syncthreads would make
-// every barrier wait for the velocity loads in flight and the stores of the
-// previous cell).  The memory clobber keeps the compiler from moving memory
-// accesses across it.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 // Element i of an array as a uniform base plus a 32-bit byte offset
 // (the scalar-base form of the global load and store): no 64-bit

@@ -689,7 +689,8 @@ int pic_mlp_grad(pic_ctx *c, const float *params, const float *x, const float *y
     if (!c || !params || batch < 1 || !x || !y || !grad) return PIC_ERR_ARG;
     CK(hipSetDevice(c->device));
     RC(ensure_ws(c, mlp_grad_scratch_floats(batch) * 4 + 1024));
-    return launch_mlp_grad(params, x, y, batch, bf16 != 0, (float *)c->ws, grad, loss, c->stream);
+    return launch_mlp_grad(params, x, y, batch, bf16 != 0, (float *)c->ws, grad, loss, nullptr,
+                           c->stream);
 }
 
 int pic_mlp_train_step(pic_ctx *c, float *params, float *adam_m, float *adam_v, int32_t t, float lr,
@@ -700,10 +701,8 @@ int pic_mlp_train_step(pic_ctx *c, float *params, float *adam_m, float *adam_v, 
     CK(hipSetDevice(c->device));
     const size_t sf = mlp_grad_scratch_floats(batch);
     RC(ensure_ws(c, (sf + 4801 + 64) * 4 + 1024));
-    float *scratch = (float *)c->ws;
-    float *grad = scratch + sf;
-    RC(launch_mlp_grad(params, x, y, batch, bf16 != 0, scratch, grad, loss, c->stream));
-    return launch_adam(params, adam_m, adam_v, grad, t, lr, c->stream);
+    const MlpAdam adam = {params, adam_m, adam_v, t, lr};
+    return launch_mlp_grad(params, x, y, batch, bf16 != 0, (float *)c->ws, nullptr, loss, &adam, c->stream);
 }
 
 int mlp_train_step(pic_ctx *c, const void *feat, const float *label, int32_t batch, void *w_master,

@@ -15,6 +15,8 @@
 //              r = || E sum_pairs 1/4 h(s^2) (|u|^2 I - 3 u u^T) || / (N T),
 //              averaged over independent re-pairings; h(s^2) = E[sin^2 Theta]
 //   training   forward, binary cross-entropy, backward and Adam, all here
+#include <math.h>
+
 #include "pic_internal.hpp"
 
 #define HIP_OK(x) do { if ((x) != hipSuccess) return PIC_ERR_HIP; } while (0)
@@ -779,75 +781,161 @@ __global__ void k_mom_select(DevGate *g, const uint64_t *step_dev, uint64_t step
 }
 
 // ------------------------------------------------------------ training
-// One block: a tile of TS samples; forward, loss and backward with the
-// activations in LDS, partial gradients written per tile and summed in a
-// fixed order by k_reduce_grads (bitwise reproducible).
+// One workgroup: a tile of TS samples; forward, loss and backward with the
+// activations in LDS, partial gradients per tile, summed in a fixed order by
+// the kernel that follows (bitwise reproducible).
+// The three products of a tile (hidden layer 2, its backward, the gradient of
+// W2: 64 x 64 x 64 each) run on 2 x 4 register tiles: 8 multiply-adds per two
+// wide LDS reads, every operand kept in the orientation in which a thread's
+// values are consecutive.  (One output per thread and step, two 4-byte reads
+// per multiply-add, was bound by the LDS: 47 us for 4,096 samples, now 16; with
+// 4 x 4 tiles on 256 threads 22 us, 1 x 4 on 1,024 threads 18, each short of
+// waves or of work per read.)  The matrix cores would add in another order and so flip the
+// bfloat16 rounding of some activations; the sums here keep the order of the
+// definition.
 constexpr int TS = 64;
+constexpr int TROW = 64 + 4;   // padded LDS rows
 
-__global__ __launch_bounds__(256) void k_mlp_grad_tile(const float *__restrict__ params,
+// n consecutive values of an LDS row (n = 1, 2 or 4, aligned to n)
+template <int N>
+__device__ __forceinline__ void row_read(float (&v)[N], const float *p)
+{
+    if constexpr (N == 4) {
+        const float4 q = *(const float4 *)p;
+        v[0] = q.x;
+        v[1] = q.y;
+        v[2] = q.z;
+        v[3] = q.w;
+    } else if constexpr (N == 2) {
+        const float2 q = *(const float2 *)p;
+        v[0] = q.x;
+        v[1] = q.y;
+    } else {
+        v[0] = *p;
+    }
+}
+constexpr int MG_T = 512;                  // threads
+constexpr int MG_R = TS * 64 / (MG_T * 4);   // rows of a thread's register tile
+
+__global__ __launch_bounds__(MG_T) void k_mlp_grad_tile(const float *__restrict__ params,
                                                       const float *__restrict__ x,
                                                       const float *__restrict__ y, int32_t B,
                                                       int bf16, float *__restrict__ partial,
                                                       float *__restrict__ loss_partial)
 {
-    __shared__ float P[NPARAM];
-    __shared__ float X[TS * 8];
-    __shared__ float Z1[TS * 64], A1[TS * 64], Z2[TS * 64], A2[TS * 64];
-    __shared__ float D3[TS];
-    __shared__ float Ls[TS];
+    __shared__ __align__(16) float W1[8 * 64], X[8][TS];             // X by feature
+    __shared__ __align__(16) float W2[64 * TROW], W2T[64 * TROW];
+    __shared__ __align__(16) float A1[TS * TROW], A1T[64 * TROW];    // by sample, by unit
+    __shared__ __align__(16) float A2[TS * TROW], A2T[64 * TROW];    // then the deltas of layer 2
+    __shared__ float b1[64], b2[64], W3[64], b3s;
+    __shared__ float D3[TS], Ls[TS];
     const bool b16 = bf16 != 0;
-    load_params(P, params, b16);
+    const int tid = threadIdx.x;
+    const int r4 = (tid >> 4) * MG_R, c4 = (tid & 15) * 4;   // the thread's MG_R x 4 tile
     const int s0 = blockIdx.x * TS;
     const int ns = min(TS, B - s0);
-    for (int e = threadIdx.x; e < TS * 8; e += blockDim.x) {
+    auto rnd = [&](float v) { return b16 ? bf16r(v) : v; };
+    for (int e = tid; e < 64 * 64; e += MG_T) {
+        const float v = rnd(params[OFF_W2 + e]);
+        W2[(e >> 6) * TROW + (e & 63)] = v;
+        W2T[(e & 63) * TROW + (e >> 6)] = v;
+    }
+    for (int e = tid; e < 8 * 64; e += MG_T) W1[e] = rnd(params[OFF_W1 + e]);
+    for (int e = tid; e < TS * 8; e += MG_T) {
         const int s = e / 8;
-        const float v = s < ns ? x[(int64_t)(s0 + s) * 8 + (e % 8)] : 0.0f;
-        X[e] = b16 ? bf16r(v) : v;
+        X[e % 8][s] = rnd(s < ns ? x[(int64_t)(s0 + s) * 8 + (e % 8)] : 0.0f);
+    }
+    if (tid < 64) {
+        b1[tid] = params[OFF_B1 + tid];
+        b2[tid] = params[OFF_B2 + tid];
+        W3[tid] = rnd(params[OFF_W3 + tid]);
+        if (tid == 0) b3s = params[OFF_B3];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < TS * 64; e += blockDim.x) {
-        const int s = e / 64, j = e % 64;
-        float z = P[OFF_B1 + j];
-        for (int i = 0; i < 8; ++i) z += X[s * 8 + i] * P[OFF_W1 + i * 64 + j];
-        Z1[e] = z;
-        const float r = z > 0.0f ? z : 0.0f;
-        A1[e] = b16 ? bf16r(r) : r;
+    // layer 1: samples r4.., units c4..
+    uint32_t on1 = 0;   // bit 4 i + j: the unit is active
+    {
+        float z[MG_R][4];
+#pragma unroll
+        for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z[i][j] = b1[c4 + j];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            float xv[MG_R], wv[4];
+            row_read<MG_R>(xv, &X[k][r4]);
+            row_read<4>(wv, &W1[k * 64 + c4]);
+#pragma unroll
+            for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) z[i][j] += xv[i] * wv[j];
+        }
+#pragma unroll
+        for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (z[i][j] > 0.0f) on1 |= 1u << (4 * i + j);
+                const float v = rnd(z[i][j] > 0.0f ? z[i][j] : 0.0f);
+                A1[(r4 + i) * TROW + c4 + j] = v;
+                A1T[(c4 + j) * TROW + r4 + i] = v;
+            }
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < TS * 64; e += blockDim.x) {
-        const int s = e / 64, j = e % 64;
-        float z = P[OFF_B2 + j];
-        for (int i = 0; i < 64; ++i) z += A1[s * 64 + i] * P[OFF_W2 + i * 64 + j];
-        Z2[e] = z;
-        const float r = z > 0.0f ? z : 0.0f;
-        A2[e] = b16 ? bf16r(r) : r;
+    // layer 2
+    uint32_t on2 = 0;
+    {
+        float z[MG_R][4];
+#pragma unroll
+        for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z[i][j] = b2[c4 + j];
+#pragma unroll 8
+        for (int k = 0; k < 64; ++k) {
+            float xv[MG_R], wv[4];
+            row_read<MG_R>(xv, &A1T[k * TROW + r4]);
+            row_read<4>(wv, &W2[k * TROW + c4]);
+#pragma unroll
+            for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) z[i][j] += xv[i] * wv[j];
+        }
+#pragma unroll
+        for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (z[i][j] > 0.0f) on2 |= 1u << (4 * i + j);
+                const float v = rnd(z[i][j] > 0.0f ? z[i][j] : 0.0f);
+                A2[(r4 + i) * TROW + c4 + j] = v;
+                A2T[(c4 + j) * TROW + r4 + i] = v;
+            }
     }
     __syncthreads();
-    if (threadIdx.x < TS) {
-        const int s = threadIdx.x;
+    // output, loss and its derivative: one thread per sample
+    if (tid < TS) {
         float d = 0.0f, l = 0.0f;
-        if (s < ns) {
-            float z = P[OFF_B3];
-            for (int j = 0; j < 64; ++j) z += A2[s * 64 + j] * P[OFF_W3 + j];
+        if (tid < ns) {
+            float z = b3s;
+#pragma unroll 16
+            for (int j = 0; j < 64; ++j) z += A2T[j * TROW + tid] * W3[j];
             const float p = 1.0f / (1.0f + __expf(-z));
-            const float t = y[s0 + s];
+            const float t = y[s0 + tid];
             l = fmaxf(z, 0.0f) - z * t + log1pf(__expf(-fabsf(z)));
             d = (p - t) / (float)B;
         }
-        D3[s] = b16 ? bf16r(d) : d;
-        Ls[s] = l;
+        D3[tid] = rnd(d);
+        Ls[tid] = l;
     }
     __syncthreads();
     float *G = partial + (int64_t)blockIdx.x * NPARAM;
-    // layer 3
-    if (threadIdx.x < 64) {
-        const int j = threadIdx.x;
+    // layer 3, and the delta of layer 2 (kept until its activations are read)
+    if (tid < 64) {
         float g = 0.0f;
-        for (int s = 0; s < TS; ++s) g += A2[s * 64 + j] * D3[s];
-        G[OFF_W3 + j] = g;
-    }
-    if (threadIdx.x == 64) {
+#pragma unroll 16
+        for (int s = 0; s < TS; ++s) g += A2[s * TROW + tid] * D3[s];
+        G[OFF_W3 + tid] = g;
+    } else if (tid == 64) {
         float g = 0.0f, l = 0.0f;
+#pragma unroll 16
         for (int s = 0; s < TS; ++s) {
             g += D3[s];
             l += Ls[s];
@@ -855,75 +943,129 @@ __global__ __launch_bounds__(256) void k_mlp_grad_tile(const float *__restrict__
         G[OFF_B3] = g;
         loss_partial[blockIdx.x] = l;
     }
+    float d2[MG_R][4];
+#pragma unroll
+    for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            d2[i][j] = rnd((on2 >> (4 * i + j)) & 1u ? W3[c4 + j] * D3[r4 + i] : 0.0f);
     __syncthreads();
-    // delta of layer 2 (overwrites Z2)
-    for (int e = threadIdx.x; e < TS * 64; e += blockDim.x) {
-        const int s = e / 64, j = e % 64;
-        const float d = Z2[e] > 0.0f ? P[OFF_W3 + j] * D3[s] : 0.0f;
-        Z2[e] = b16 ? bf16r(d) : d;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < 64 * 64; e += blockDim.x) {
-        const int i = e / 64, j = e % 64;
-        float g = 0.0f;
-        for (int s = 0; s < TS; ++s) g += A1[s * 64 + i] * Z2[s * 64 + j];
-        G[OFF_W2 + e] = g;
-    }
-    if (threadIdx.x < 64) {
-        float g = 0.0f;
-        for (int s = 0; s < TS; ++s) g += Z2[s * 64 + threadIdx.x];
-        G[OFF_B2 + threadIdx.x] = g;
-    }
-    // delta of layer 1 (overwrites Z1)
-    for (int e = threadIdx.x; e < TS * 64; e += blockDim.x) {
-        const int s = e / 64, i = e % 64;
-        float d = 0.0f;
-        if (Z1[e] > 0.0f) {
-            for (int j = 0; j < 64; ++j) d += P[OFF_W2 + i * 64 + j] * Z2[s * 64 + j];
+    float *D2 = A2, *D2T = A2T;
+#pragma unroll
+    for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            D2[(r4 + i) * TROW + c4 + j] = d2[i][j];
+            D2T[(c4 + j) * TROW + r4 + i] = d2[i][j];
         }
-        Z1[e] = b16 ? bf16r(d) : d;
+    __syncthreads();
+    // gradient of W2 (rows r4.., columns c4..) and the delta of layer 1
+    // (samples r4.., units c4..)
+    {
+        float g[MG_R][4] = {};
+#pragma unroll 8
+        for (int s = 0; s < TS; ++s) {
+            float xv[MG_R], wv[4];
+            row_read<MG_R>(xv, &A1[s * TROW + r4]);
+            row_read<4>(wv, &D2[s * TROW + c4]);
+#pragma unroll
+            for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) g[i][j] += xv[i] * wv[j];
+        }
+#pragma unroll
+        for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) G[OFF_W2 + (r4 + i) * 64 + c4 + j] = g[i][j];
+    }
+    float *D1 = A1T;   // by sample (layer 2 has read the activations)
+    {
+        float d[MG_R][4] = {};
+#pragma unroll 8
+        for (int k = 0; k < 64; ++k) {
+            float xv[MG_R], wv[4];
+            row_read<MG_R>(xv, &D2T[k * TROW + r4]);
+            row_read<4>(wv, &W2T[k * TROW + c4]);
+#pragma unroll
+            for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d[i][j] += wv[j] * xv[i];
+        }
+#pragma unroll
+        for (int i = 0; i < MG_R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                D1[(r4 + i) * TROW + c4 + j] = rnd((on1 >> (4 * i + j)) & 1u ? d[i][j] : 0.0f);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < 8 * 64; e += blockDim.x) {
+    for (int e = tid; e < 8 * 64; e += MG_T) {
         const int i = e / 64, j = e % 64;
         float g = 0.0f;
-        for (int s = 0; s < TS; ++s) g += X[s * 8 + i] * Z1[s * 64 + j];
+#pragma unroll 16
+        for (int s = 0; s < TS; ++s) g += X[i][s] * D1[s * TROW + j];
         G[OFF_W1 + e] = g;
     }
-    if (threadIdx.x < 64) {
+    if (tid < 64) {
         float g = 0.0f;
-        for (int s = 0; s < TS; ++s) g += Z1[s * 64 + threadIdx.x];
-        G[OFF_B1 + threadIdx.x] = g;
+#pragma unroll 16
+        for (int s = 0; s < TS; ++s) g += D1[s * TROW + tid];
+        G[OFF_B1 + tid] = g;
+    } else if (tid < 128) {
+        const int j = tid - 64;
+        float g = 0.0f;
+#pragma unroll 16
+        for (int s = 0; s < TS; ++s) g += D2[s * TROW + j];
+        G[OFF_B2 + j] = g;
     }
 }
 
-__global__ void k_reduce_grads(const float *__restrict__ partial, const float *__restrict__ loss_partial,
-                               int tiles, int32_t B, float *__restrict__ grad, float *__restrict__ loss)
+// Sum of the tiles' partial gradients, and with adam.m the optimiser's step on
+// it (Adam of Kingma & Ba with bias correction, step t >= 1) in the same pass.
+// A workgroup takes RG_P parameters: RG_G groups of threads each add every
+// RG_G-th tile (their loads in flight together), then the groups are added in
+// order.  (One thread adding a parameter's tiles one after another waited for
+// 64 loads in a row: 18.5 us for 4,096 samples.)
+constexpr int RG_P = 32, RG_G = 16;
+
+struct AdamArgs {
+    float *params, *m, *v;   // m null: gradient only
+    float c1, c2, lr, b1, b2, eps;
+};
+
+__global__ __launch_bounds__(RG_P * RG_G) void k_reduce_grads(const float *__restrict__ partial,
+                                                              const float *__restrict__ loss_partial, int tiles,
+                                                              int32_t B, float *__restrict__ grad,
+                                                              float *__restrict__ loss, AdamArgs o)
 {
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < NPARAM; p += gridDim.x * blockDim.x) {
-        float g = 0.0f;
-        for (int t = 0; t < tiles; ++t) g += partial[(int64_t)t * NPARAM + p];
-        grad[p] = g;
+    __shared__ float red[RG_G][RG_P];
+    const int pi = threadIdx.x % RG_P, gi = threadIdx.x / RG_P;
+    const int p = blockIdx.x * RG_P + pi;
+    float s = 0.0f;
+    if (p < NPARAM) {
+#pragma unroll 4
+        for (int t = gi; t < tiles; t += RG_G) s += partial[(int64_t)t * NPARAM + p];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
+    red[gi][pi] = s;
+    __syncthreads();
+    if (gi == 0 && p < NPARAM) {
+        float g = 0.0f;
+#pragma unroll
+        for (int q = 0; q < RG_G; ++q) g += red[q][pi];
+        if (grad) grad[p] = g;
+        if (o.m) {
+            const float mm = o.b1 * o.m[p] + (1.0f - o.b1) * g;
+            const float vv = o.b2 * o.v[p] + (1.0f - o.b2) * g * g;
+            o.m[p] = mm;
+            o.v[p] = vv;
+            o.params[p] -= o.lr * (mm / o.c1) / (sqrtf(vv / o.c2) + o.eps);
+        }
+    }
+    if (blockIdx.x == 0 && loss && threadIdx.x / PIC_WAVE == 1) {
+        // the second wave: the mean loss, tiles by lane, lanes by a fixed tree
         float l = 0.0f;
-        for (int t = 0; t < tiles; ++t) l += loss_partial[t];
-        *loss = l / (float)B;
-    }
-}
-
-// Adam (Kingma & Ba) with bias correction, step t >= 1.
-__global__ void k_adam(float *__restrict__ params, float *__restrict__ m, float *__restrict__ v,
-                       const float *__restrict__ grad, int32_t t, float lr, float b1, float b2, float eps)
-{
-    const float c1 = 1.0f - powf(b1, (float)t), c2 = 1.0f - powf(b2, (float)t);
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < NPARAM; p += gridDim.x * blockDim.x) {
-        const float g = grad[p];
-        const float mm = b1 * m[p] + (1.0f - b1) * g;
-        const float vv = b2 * v[p] + (1.0f - b2) * g * g;
-        m[p] = mm;
-        v[p] = vv;
-        params[p] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
+        for (int t = (int)threadIdx.x - PIC_WAVE; t < tiles; t += PIC_WAVE) l += loss_partial[t];
+        l = wave_sum(l);
+        if (threadIdx.x == PIC_WAVE) *loss = l / (float)B;
     }
 }
 
@@ -983,23 +1125,24 @@ size_t mlp_grad_scratch_floats(int32_t B)
 }
 
 int launch_mlp_grad(const float *params, const float *x, const float *y, int32_t B, int bf16,
-                    float *scratch, float *grad, float *loss, hipStream_t st)
+                    float *scratch, float *grad, float *loss, const MlpAdam *adam, hipStream_t st)
 {
     const int tiles = (B + TS - 1) / TS;
     float *partial = scratch;
     float *lp = scratch + (size_t)tiles * NPARAM;
-    hipLaunchKernelGGL(k_mlp_grad_tile, dim3(tiles), dim3(256), 0, st, params, x, y, B, bf16, partial, lp);
-    hipLaunchKernelGGL(k_reduce_grads, dim3((NPARAM + 255) / 256), dim3(256), 0, st, partial, lp, tiles,
-                       B, grad, loss);
-    HIP_OK(hipGetLastError());
-    return PIC_OK;
-}
-
-int launch_adam(float *params, float *m, float *v, const float *grad, int32_t t, float lr,
-                hipStream_t st)
-{
-    hipLaunchKernelGGL(k_adam, dim3((NPARAM + 255) / 256), dim3(256), 0, st, params, m, v, grad, t, lr,
-                       0.9f, 0.999f, 1e-8f);
+    AdamArgs o = {nullptr, nullptr, nullptr, 1.0f, 1.0f, 0.0f, 0.9f, 0.999f, 1e-8f};
+    if (adam) {
+        o.params = adam->params;
+        o.m = adam->m;
+        o.v = adam->v;
+        o.lr = adam->lr;
+        // the bias corrections, in binary32 as the parameters
+        o.c1 = 1.0f - powf(o.b1, (float)adam->t);
+        o.c2 = 1.0f - powf(o.b2, (float)adam->t);
+    }
+    hipLaunchKernelGGL(k_mlp_grad_tile, dim3(tiles), dim3(MG_T), 0, st, params, x, y, B, bf16, partial, lp);
+    hipLaunchKernelGGL(k_reduce_grads, dim3((NPARAM + RG_P - 1) / RG_P), dim3(RG_P * RG_G), 0, st, partial, lp,
+                       tiles, B, grad, loss, o);
     HIP_OK(hipGetLastError());
     return PIC_OK;
 }

@@ -944,10 +944,15 @@ int launch_mlp_forward(const float *params, const float *x, int32_t B, int bf16,
 int launch_gate_infer_decide(const float *prob, int32_t M, float thr, int32_t kmax, uint8_t *skip,
                              int32_t *k_acc, hipStream_t st);
 size_t mlp_grad_scratch_floats(int32_t B);
+// The optimiser's step fused into the gradient's reduction.
+struct MlpAdam {
+    float *params, *m, *v;
+    int32_t t;
+    float lr;
+};
+// grad nullable; adam nullable (gradient only).
 int launch_mlp_grad(const float *params, const float *x, const float *y, int32_t B, int bf16,
-                    float *scratch, float *grad, float *loss, hipStream_t st);
-int launch_adam(float *params, float *m, float *v, const float *grad, int32_t t, float lr,
-                hipStream_t st);
+                    float *scratch, float *grad, float *loss, const MlpAdam *adam, hipStream_t st);
 int launch_gate(const GateArgs &a, hipStream_t st);
 int launch_analytic_relax(const double *moments, int32_t M, double dt, double lnL, const double *density,
                           int replicas, double *r, hipStream_t st);

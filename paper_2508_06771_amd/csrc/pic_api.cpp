@@ -51,7 +51,7 @@ struct pic_ctx {
     double mcc_sigma0 = 0.0, mcc_nn = 0.0, mcc_mr = 0.0;
     // DSMC-Coll cross-section table (device copy) and its host header
     double *dsmc_buf = nullptr;
-    DsmcTable dsmc_tab = {0, nullptr, nullptr, {0, 0, 0, 0}, 0.0};
+    DsmcTable dsmc_tab = {0, nullptr, nullptr, {0, 0, 0, 0}, 0.0, nullptr, 0};
     bool mcc_set = false;
     double *moments_out = nullptr;
     // graph of one steady-state step (pic_run_steps)
@@ -420,8 +420,10 @@ int pic_set_dsmc(pic_ctx *c, int32_t nseg, const double *breaks, const double *c
     for (int k = 0; k < 4; ++k)
         if (!(threshold[k] >= 0.0)) return PIC_ERR_ARG;
     CK(hipSetDevice(c->device));
-    const size_t nb = (size_t)(nseg + 1) + (size_t)4 * nseg * 4;
+    const size_t nt = (size_t)(nseg + 1) + (size_t)4 * nseg * 4;   // the table, then the bounds
+    const size_t nb = nt + DSMC_BINS;                              // (two binary32 per bin)
     std::vector<double> host(nb);
+    c->dsmc_tab.bin0 = dsmc_bounds(nseg, breaks, coef, threshold, (float *)(host.data() + nt));
     memcpy(host.data(), breaks, (size_t)(nseg + 1) * sizeof(double));
     memcpy(host.data() + nseg + 1, coef, (size_t)4 * nseg * 4 * sizeof(double));
     CK(hipStreamSynchronize(c->stream));
@@ -432,6 +434,7 @@ int pic_set_dsmc(pic_ctx *c, int32_t nseg, const double *breaks, const double *c
     c->dsmc_tab.nseg = nseg;
     c->dsmc_tab.breaks = c->dsmc_buf;
     c->dsmc_tab.coef = c->dsmc_buf + nseg + 1;
+    c->dsmc_tab.upper = (const float *)(c->dsmc_buf + nt);
     for (int k = 0; k < 4; ++k) c->dsmc_tab.thr[k] = threshold[k];
     c->dsmc_tab.mass_ratio = mass_ratio;
     return PIC_OK;
@@ -474,7 +477,7 @@ int dsmc_collide(pic_ctx *c, int dtype, void *v, const int32_t *cell_of, const u
     a.chan_out = channel_out;
     a.dflags = c->flags;
     ktime_begin(KT_DSMC, c->stream);
-    const int rc = launch_dsmc(dtype, a, c->dsmc_tab, c->stream);
+    const int rc = launch_dsmc(dtype, a, c->dsmc_tab, c->num_cu, c->stream);
     ktime_end(KT_DSMC, c->stream);
     return rc;
 }

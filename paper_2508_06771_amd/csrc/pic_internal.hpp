@@ -983,7 +983,15 @@ struct DsmcTable {
     const double *coef;     // device [4][nseg][4]
     double thr[4];
     double mass_ratio;
+    const float *upper;     // device [DSMC_BINS][2]: upper bounds of the cross sections on
+                            // the ground state and on the metastable density per energy bin
+    int bin0;               // leading bits of the first bin's energy
 };
+// Energy bins of the screen: an eighth of an octave (the leading 11 bits of the
+// binary32 energy without its sign).
+constexpr int DSMC_BINS = 256, DSMC_BIN_SHIFT = 20;
+// Fills upper (host, [DSMC_BINS][2]) from a table's host arrays; returns bin0.
+int dsmc_bounds(int nseg, const double *breaks, const double *coef, const double *thr, float *upper);
 struct DsmcArgs {
     void *v;
     int64_t n;
@@ -1002,7 +1010,7 @@ struct DsmcArgs {
     uint8_t *chan_out;
     DevFlags *dflags;
 };
-int launch_dsmc(int dtype, const DsmcArgs &a, const DsmcTable &t, hipStream_t st);
+int launch_dsmc(int dtype, const DsmcArgs &a, const DsmcTable &t, int num_cu, hipStream_t st);
 
 // Recombination C5 on cell-sorted storage (v and w of the velocity dtype).
 struct RecombArgs {

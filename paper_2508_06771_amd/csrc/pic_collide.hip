@@ -963,6 +963,17 @@ __device__ __forceinline__ int opaque(int n)
     return n;
 }
 
+// Segment of a key among S equal key ranges, and the key's position inside
+// its range scaled to 32 bits (order-preserving within the segment).
+__device__ __forceinline__ uint32_t seg_of(uint32_t key, uint32_t S)
+{
+    return (uint32_t)(((uint64_t)key * S) >> 32);
+}
+__device__ __forceinline__ uint32_t seg_key(uint32_t key, uint32_t S)
+{
+    return (uint32_t)((uint64_t)key * S);
+}
+
 // Counting sort of a cell's members by (key, pid) in LDS, shared by the lean
 // passes (n >= 2): one Philox call per member (key, words 2 and 3, the
 // null-collision candidate bit; cpid: the pid of the thread's first
@@ -970,11 +981,13 @@ __device__ __forceinline__ int opaque(int n)
 // member), scan, placement, rank inside the buckets.  On entry pos[k] holds
 // member k's pid, on return its position in the cell's sorted order.
 // Contains the barriers; the sort's memory is free after a further barrier.
-template <int T, int K, bool MCC, bool CLEAR2 = false>
+// With SEG the members are those of one of a cell's S segments: the key is
+// its position inside the segment's range (see seg_key).
+template <int T, int K, bool MCC, bool CLEAR2 = false, bool SEG = false>
 __device__ __forceinline__ void lean_sort(const CollideArgs &a, int n, uint32_t step,
                                           const uint32_t *pid_c, unsigned char *smem, uint32_t *wtot,
                                           uint32_t (&w2)[K], uint32_t (&w3)[K], uint32_t (&key)[K],
-                                          uint32_t (&pos)[K], uint32_t &cand, uint32_t &cpid)
+                                          uint32_t (&pos)[K], uint32_t &cand, uint32_t &cpid, uint32_t S = 1u)
 {
     typedef LeanGeom<T, K> G;
     const uint32_t bits = sort_bits(n);
@@ -1002,14 +1015,14 @@ __device__ __forceinline__ void lean_sort(const CollideArgs &a, int n, uint32_t 
         const int i = threadIdx.x + k * T;
         if (i < n1) {
             const W4 w = draw4(a.seed, pos[k], step, 0u, 0u);
-            key[k] = w.x;
+            key[k] = SEG ? seg_key(w.x, S) : w.x;
             w2[k] = w.z;
             w3[k] = w.w;
             if (MCC && (uint64_t)w.y < a.mcc_thr) {
                 if (!cand) cpid = pos[k];
                 cand |= 1u << k;
             }
-            const uint32_t b = w.x >> (32u - bits);
+            const uint32_t b = key[k] >> (32u - bits);
             pos[k] = atomicAdd(&cnt[b], 1u);   // arrival rank in the bucket
         }
     }
@@ -1088,23 +1101,28 @@ struct LeanNext {
     float *sink;               // 64 words of LDS
 };
 
+// n entries of pid and of `arrays` further arrays of dwords, stride apart.
+template <int T>
+__device__ __forceinline__ void prefetch_run(const uint32_t *pid, uint32_t arrays, const float *v, size_t stride,
+                                             int n, float *sink)
+{
+    if (n <= 0) return;
+    // 128-byte lines of each of the arrays (one more for a start inside a
+    // line); one dword per line
+    const uint32_t lines = ((uint32_t)n + 31u) / 32u + 1u;
+    for (uint32_t t = threadIdx.x; t < (arrays + 1u) * lines; t += T) {
+        const uint32_t arr = t / lines, l = t - arr * lines;
+        const uint32_t idx = min(l * 32u, (uint32_t)n - 1u);
+        const float *p = arr == 0 ? (const float *)(pid + idx) : v + (size_t)(arr - 1u) * stride + idx;
+        __builtin_amdgcn_global_load_lds((const void *)p, (__attribute__((address_space(3))) void *)sink,
+                                         4, 0, 0);
+    }
+}
 template <int T>
 __device__ __forceinline__ void prefetch_cell(const CollideArgs &a, int cell, float *sink)
 {
     const int lo = a.cell_start[cell];
-    const int n = a.cell_start[cell + 1] - lo;
-    if (n <= 0) return;
-    // 128-byte lines of each of the four arrays (one more for a start
-    // inside a line); one dword per line
-    const uint32_t lines = ((uint32_t)n + 31u) / 32u + 1u;
-    for (uint32_t t = threadIdx.x; t < 4u * lines; t += T) {
-        const uint32_t arr = t / lines, l = t - arr * lines;
-        const uint32_t idx = (uint32_t)lo + min(l * 32u, (uint32_t)n - 1u);
-        const float *p = arr == 0 ? (const float *)(a.pid + idx)
-                                  : (const float *)a.v + (size_t)(arr - 1u) * (size_t)a.n + idx;
-        __builtin_amdgcn_global_load_lds((const void *)p, (__attribute__((address_space(3))) void *)sink,
-                                         4, 0, 0);
-    }
+    prefetch_run<T>(a.pid + lo, 3u, (const float *)a.v + lo, (size_t)a.n, a.cell_start[cell + 1] - lo, sink);
 }
 
 // With nx, the pass also takes the next work item from the queue and
@@ -1698,26 +1716,28 @@ __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int3
 
 // ------------------------------------------------------------ segmented cells
 // Cells beyond the largest LDS class with several workgroups each (see
-// SegScratch): count members per segment, scan, copy members segment-major,
+// SegScratch): count members per segment, scan, copy ids and slots segment-major,
 // sort and pair each segment in LDS, then the pairs across segment edges.
-constexpr int SEG_CT = 256;   // threads of the counting and copying kernels
-constexpr int SEG_U = 8;      // members per thread whose loads are in flight together
-
-// Segment of a key among S equal key ranges, and the key's position inside
-// its range scaled to 32 bits (order-preserving within the segment).
-__device__ __forceinline__ uint32_t seg_of(uint32_t key, uint32_t S)
-{
-    return (uint32_t)(((uint64_t)key * S) >> 32);
-}
-__device__ __forceinline__ uint32_t seg_key(uint32_t key, uint32_t S)
-{
-    return (uint32_t)((uint64_t)key * S);
-}
+// The counting and copying kernels: one work item's members are one batch of
+// SEG_U per thread, all loads in flight together.
+constexpr int SEG_CT = 1024;
+constexpr int SEG_U = SEG_CHUNK / SEG_CT;
+static_assert(SEG_U * SEG_CT == SEG_CHUNK, "a work item is one batch");
 
 struct SegItem {
     int h, lo, b, e;
     uint32_t S;
 };
+
+// Cells of at most this many segments are not copied: their segments' passes
+// gather the velocities by storage slot, which saves 24 bytes a member of the
+// copy (in binary32).  A gather finds its neighbours' lines in the XCD's L2 as
+// long as a line's members belong to segments worked on together (32 a XCD);
+// with thousands of segments every load is a line of its own.  Copied against
+// gathered, the whole path: 100 cells of 90,000 346 / 315 us, 1,000 of 12,000
+// 357 / 324, one of 2,000,000 (224 segments) 210 / 193, one of 20,000,000
+// (2,233) 2,234 / 2,390; binary64, 100 of 40,000 426 / 350.
+constexpr uint32_t SEG_GATHER = 1024;
 
 // Work item -> its cell h of the list, the cell's first slot and the item's
 // member range [b, e) inside the cell.
@@ -1729,8 +1749,11 @@ __device__ __forceinline__ SegItem seg_item(const CollideArgs &a, const SegScrat
     const int cell = list[it.h];
     it.lo = a.cell_start[cell];
     const int n = a.cell_start[cell + 1] - it.lo;
-    it.b = (int)(item - (uint32_t)ss.hc_chunk[it.h]) * SEG_CHUNK;
-    it.e = min(n, it.b + SEG_CHUNK);
+    // equal parts of whole 128-byte lines of a binary32 array
+    const int parts = (n + SEG_CHUNK - 1) / SEG_CHUNK;
+    const int per = ((n + parts - 1) / parts + 31) & ~31;
+    it.b = min(n, (int)(item - (uint32_t)ss.hc_chunk[it.h]) * per);
+    it.e = min(n, it.b + per);
     it.S = ss.hc_S[it.h];
     return it;
 }
@@ -1749,20 +1772,14 @@ __global__ __launch_bounds__(SEG_CT) void k_seg_count(CollideArgs a, const int32
         const uint32_t S = it.S;
         for (uint32_t q = threadIdx.x; q < S; q += SEG_CT) hist[q] = 0u;
         __syncthreads();
-        // SEG_U members per thread per round, their pids loaded together
-        for (int i0 = it.b + (int)threadIdx.x; i0 < it.e; i0 += SEG_U * SEG_CT) {
-            uint32_t pv[SEG_U];
+        uint32_t pv[SEG_U];
 #pragma unroll
-            for (int u = 0; u < SEG_U; ++u) {
-                const int i = i0 + u * SEG_CT;
-                if (i < it.e) pv[u] = a.pid[it.lo + i];
-            }
+        for (int u = 0; u < SEG_U; ++u)
+            pv[u] = ld_at(a.pid + it.lo, (uint32_t)min(it.b + (int)threadIdx.x + u * SEG_CT, it.e - 1));
 #pragma unroll
-            for (int u = 0; u < SEG_U; ++u) {
-                const int i = i0 + u * SEG_CT;
-                if (i < it.e) atomicAdd(&hist[seg_of(draw4(a.seed, pv[u], step, 0u, 0u).x, S)], 1u);
-            }
-        }
+        for (int u = 0; u < SEG_U; ++u)
+            if (it.b + (int)threadIdx.x + u * SEG_CT < it.e)
+                atomicAdd(&hist[seg_of(draw4(a.seed, pv[u], step, 0u, 0u).x, S)], 1u);
         __syncthreads();
         const int32_t sb = ss.hc_seg[it.h];
         for (uint32_t q = threadIdx.x; q < S; q += SEG_CT)
@@ -1800,82 +1817,75 @@ __global__ __launch_bounds__(1024) void k_seg_scan(CollideArgs a, SegScratch ss,
     }
 }
 
-// Members to their segment's run: counts per segment in LDS, one global
-// reservation per non-empty segment, then each member at its reservation
-// plus its LDS arrival rank (the order inside a run is free: the segment
-// pass sorts by key and pid).
+// Members to their segment's run: each member's arrival rank in its segment
+// from an LDS counter, one global reservation per non-empty segment, then each
+// member at its reservation plus its rank (the order inside a run is free: the
+// segment pass sorts by key and pid).  Bound by its bytes (36 a member in
+// binary32): one read of the members, ids and velocities together, with the
+// ranks kept in registers, on 32 waves a CU (256 threads, two reads and two
+// counts: 93 us for the cells beyond 10,240 members of a log-normal 40M
+// electrons; copying ids and slots only, now 53).
 template <typename R>
 __global__ __launch_bounds__(SEG_CT) void k_seg_scatter(CollideArgs a, const int32_t *__restrict__ list,
                                                         SegScratch ss)
 {
-    __shared__ uint32_t hist[SEG_MAX];
-    __shared__ uint32_t base[SEG_MAX];
-    __shared__ uint16_t sof[SEG_CHUNK];
+    __shared__ uint32_t hist[SEG_MAX];   // counts, then the first slots reserved
     if (gated_off(a)) return;
     const uint32_t items = a.dflags->count[CHUNK_SLOT];
     const uint32_t step = (uint32_t)read_step(a);
-    const R *v = (const R *)a.v;
-    R *mv = (R *)ss.m_v;
     for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
         const SegItem it = seg_item(a, ss, list, item);
         if (ss.hc_fb[it.h]) continue;   // the same for the whole workgroup
-        const uint32_t S = it.S;
-        for (uint32_t q = threadIdx.x; q < S; q += SEG_CT) hist[q] = 0u;
-        __syncthreads();
-        for (int i0 = it.b + (int)threadIdx.x; i0 < it.e; i0 += SEG_U * SEG_CT) {
-            uint32_t pv[SEG_U];
-#pragma unroll
-            for (int u = 0; u < SEG_U; ++u) {
-                const int i = i0 + u * SEG_CT;
-                if (i < it.e) pv[u] = a.pid[it.lo + i];
-            }
-#pragma unroll
-            for (int u = 0; u < SEG_U; ++u) {
-                const int i = i0 + u * SEG_CT;
-                if (i < it.e) {
-                    const uint32_t q = seg_of(draw4(a.seed, pv[u], step, 0u, 0u).x, S);
-                    sof[i - it.b] = (uint16_t)q;
-                    atomicAdd(&hist[q], 1u);
-                }
-            }
-        }
-        __syncthreads();
+        // the cell's members and its run in the scratch (indices within a cell
+        // fit the 32-bit offsets of ld_at and st_at)
         const int32_t sb = ss.hc_seg[it.h];
-        for (uint32_t q = threadIdx.x; q < S; q += SEG_CT) {
-            base[q] = hist[q] ? atomicAdd(&ss.sg_cur[sb + q], hist[q]) : 0u;
-            hist[q] = 0u;
-        }
-        __syncthreads();
-        for (int i0 = it.b + (int)threadIdx.x; i0 < it.e; i0 += SEG_U * SEG_CT) {
-            uint32_t pv[SEG_U];
-            R x[SEG_U], y[SEG_U], z[SEG_U];
+        const uint32_t run = ss.sg_start[sb];
+        const R *v = (const R *)a.v + it.lo;
+        R *mv = (R *)ss.m_v + run;
+        const uint32_t S = it.S;
+        uint32_t pv[SEG_U], q[SEG_U];
+        R x[SEG_U], y[SEG_U], z[SEG_U];
+        const bool copy = S > SEG_GATHER;
 #pragma unroll
-            for (int u = 0; u < SEG_U; ++u) {
-                const int64_t g = (int64_t)it.lo + i0 + u * SEG_CT;
-                if (i0 + u * SEG_CT < it.e) {
-                    pv[u] = a.pid[g];
-                    x[u] = v[g];
-                    y[u] = v[a.n + g];
-                    z[u] = v[2 * a.n + g];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SEG_U; ++u) {
-                const int i = i0 + u * SEG_CT;
-                if (i < it.e) {
-                    const uint32_t q = sof[i - it.b];
-                    const uint32_t slot = base[q] + atomicAdd(&hist[q], 1u);
-                    ss.m_orig[slot] = it.lo + i;
-                    ss.m_pid[slot] = pv[u];
-                    mv[slot] = x[u];
-                    mv[ss.m_stride + slot] = y[u];
-                    mv[2 * ss.m_stride + slot] = z[u];
-                }
+        for (int u = 0; u < SEG_U; ++u) {
+            const uint32_t i = (uint32_t)min(it.b + (int)threadIdx.x + u * SEG_CT, it.e - 1);
+            pv[u] = ld_at(a.pid + it.lo, i);
+            if (copy) {
+                x[u] = ld_at(v, i);
+                y[u] = ld_at(v + a.n, i);
+                z[u] = ld_at(v + 2 * a.n, i);
             }
         }
-        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < S; j += SEG_CT) hist[j] = 0u;
+        lds_barrier();
+#pragma unroll
+        for (int u = 0; u < SEG_U; ++u) {
+            q[u] = seg_of(draw4(a.seed, pv[u], step, 0u, 0u).x, S);
+            // segment (12 bits) and arrival rank (below SEG_CHUNK)
+            if (it.b + (int)threadIdx.x + u * SEG_CT < it.e) q[u] |= atomicAdd(&hist[q[u]], 1u) << 16;
+        }
+        lds_barrier();
+        for (uint32_t j = threadIdx.x; j < S; j += SEG_CT)
+            if (hist[j]) hist[j] = atomicAdd(&ss.sg_cur[sb + j], hist[j]) - run;
+        lds_barrier();
+#pragma unroll
+        for (int u = 0; u < SEG_U; ++u) {
+            const int i = it.b + (int)threadIdx.x + u * SEG_CT;
+            if (i < it.e) {
+                const uint32_t slot = hist[q[u] & 0xffffu] + (q[u] >> 16);
+                st_at(ss.m_orig + run, slot, it.lo + i);
+                st_at(ss.m_pid + run, slot, pv[u]);
+                if (copy) {
+                    st_at(mv, slot, x[u]);
+                    st_at(mv + ss.m_stride, slot, y[u]);
+                    st_at(mv + 2 * ss.m_stride, slot, z[u]);
+                }
+            }
+        }
+        lds_barrier();
     }
 }
+static_assert(SEG_MAX <= 1 << 16 && SEG_CHUNK <= 1 << 16, "segment and rank share a word");
 
 // One segment: the members of run [start, start + n) sort by key (by their
 // position inside the segment's key range, scaled to 32 bits, whose top bits
@@ -1912,6 +1922,7 @@ __device__ __forceinline__ void seg_pass(const CollideArgs &a, const int32_t *li
     R *vy_g = vx_g + a.n;
     R *vz_g = vy_g + a.n;
     const SortLDS<T, CAP> L(smem);
+    const bool gather = S <= SEG_GATHER;
 
     R vx[K], vy[K], vz[K];
     uint32_t w2[K], w3[K], pos[K];
@@ -1922,9 +1933,16 @@ __device__ __forceinline__ void seg_pass(const CollideArgs &a, const int32_t *li
         const int i = threadIdx.x + k * T;
         if (i < (int)n) {
             pos[k] = pid_s[i];
-            vx[k] = mx[i];
-            vy[k] = my[i];
-            vz[k] = mz[i];
+            if (gather) {
+                const int32_t g = orig[i];
+                vx[k] = vx_g[g];
+                vy[k] = vy_g[g];
+                vz[k] = vz_g[g];
+            } else {
+                vx[k] = mx[i];
+                vy[k] = my[i];
+                vz[k] = mz[i];
+            }
         }
     }
     L.clear();
@@ -2051,21 +2069,180 @@ __device__ __forceinline__ void seg_pass(const CollideArgs &a, const int32_t *li
     __syncthreads();
 }
 
+// Work items in order of arrival -> segments such that the items of one
+// remainder mod 8 (the workgroups of one XCD take them) are neighbouring
+// segments: the scattered stores of a cell's segments then meet in one L2.
+__device__ __forceinline__ uint32_t xcd_run(uint32_t item, uint32_t count)
+{
+    const uint32_t q = count / 8u, r = count % 8u, x = item % 8u;
+    return x * q + min(x, r) + item / 8u;
+}
+
+// The same in binary32, on the lean pass's sort and exchange rounds: positions
+// count from the first one paired inside the segment, so the member paired
+// across the lower edge has position -1 and takes part in no round; the one
+// paired across the upper edge is the round's unpaired last one.  With nx the
+// next segment's members are requested meanwhile, and the next work item is
+// returned (see lean_pass).  The large cells of a log-normal 40M electrons:
+// 164 us (the class kernels' sort and exchange on copied members 180).
+template <int T, int K, int F>
+__device__ __forceinline__ int lean_seg_pass(const CollideArgs &a, const int32_t *list, const SegScratch &ss,
+                                             uint32_t seg, unsigned char *smem, uint32_t *wtot,
+                                             const LeanNext *nx = nullptr)
+{
+    constexpr bool MCC = (F & F_MCC) != 0;
+    constexpr uint32_t P = LeanExch<T, K, F>::P;
+    const int h = ss.sg_cell[seg];
+    const int n = (int)ss.sg_cnt[seg];
+    const uint32_t step = (uint32_t)read_step(a);
+    if (ss.hc_fb[h] || n == 0) {
+        if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
+        lds_barrier();
+        const int next = nx ? *nx->slot : 0;
+        lds_barrier();
+        return next;
+    }
+    const int cell = list[h];
+    const int lo_c = a.cell_start[cell];
+    const uint32_t n_c = (uint32_t)(a.cell_start[cell + 1] - lo_c);
+    const uint32_t start = ss.sg_start[seg];
+    const uint32_t off = start - ss.sg_start[ss.hc_seg[h]];
+    const uint32_t S = ss.hc_S[h];
+    const uint32_t *pid_s = ss.m_pid + start;
+
+    float vx[K], vy[K], vz[K];
+    float wt[1];
+    uint32_t w2[K], w3[K], key[K], pos[K];
+    uint32_t cand = 0, cpid = 0;
+    {
+        uint32_t ic[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) ic[k] = (uint32_t)min((int)threadIdx.x + k * T, n - 1);
+#pragma unroll
+        for (int k = 0; k < K; ++k) pos[k] = ld_at(pid_s, ic[k]);
+        asm volatile("" ::: "memory");   // keep the id loads ahead of the velocity loads
+        // the copy, or the members in their storage slots
+        const float *mx = (const float *)ss.m_v + start;
+        size_t stride = (size_t)ss.m_stride;
+        if (S <= SEG_GATHER) {
+            mx = (const float *)a.v + lo_c;
+            stride = (size_t)a.n;
+#pragma unroll
+            for (int k = 0; k < K; ++k) ic[k] = (uint32_t)(ld_at(ss.m_orig + start, ic[k]) - lo_c);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            vx[k] = ld_at(mx, ic[k]);
+            vy[k] = ld_at(mx + stride, ic[k]);
+            vz[k] = ld_at(mx + 2 * stride, ic[k]);
+        }
+    }
+    if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
+    if (n >= 2) {
+        lean_sort<T, K, MCC, true, true>(a, n, step, pid_s, smem, wtot, w2, w3, key, pos, cand, cpid, S);
+    } else {
+        // a lone member: only its null collision and its place are needed
+        const W4 w = draw4(a.seed, pos[0], step, 0u, 0u);
+        if (MCC && threadIdx.x == 0 && (uint64_t)w.y < a.mcc_thr) {
+            cpid = pos[0];
+            cand = 1u;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            w2[k] = w.z;
+            w3[k] = w.w;
+            pos[k] = 0u;
+        }
+    }
+    lds_barrier();   // the sort's memory becomes the exchange records
+
+    // pairs inside the segment cover local positions [first, first + np2)
+    const uint32_t first = off & 1u;
+    const uint32_t np2 = ((uint32_t)n - first) & ~1u;
+    const bool tail = off + first + np2 + 1u < n_c;   // the position after them has its partner above
+    const int kf = cand ? __builtin_ctz(cand) : K;
+    uint32_t edge = 0;   // bit k: the partner is in a neighbouring segment
+    const int n1 = opaque(n);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int i = threadIdx.x + k * T;
+        pos[k] -= first;
+        if (i < n1) {
+            if (pos[k] == 0xffffffffu) {
+                edge |= 1u << k;
+                ss.bnd_head[seg] = (int32_t)(start + i);
+            } else if (tail && pos[k] == np2) {
+                edge |= 1u << k;
+                ss.bnd_tail[seg] = (int32_t)(start + i);
+            }
+        }
+    }
+    if constexpr (MCC) cand &= ~edge;
+    const float C = (float)cell_C(a, cell);
+    if (nx) {
+        asm volatile("" ::"v"(C));   // complete before the requests below
+        const uint32_t nxt = (uint32_t)*nx->slot;
+        if (nxt < nx->count) {
+            const uint32_t s2 = xcd_run(nxt, nx->count);
+            const uint32_t st = ss.sg_start[s2];
+            const int n2 = (int)ss.sg_cnt[s2];
+            prefetch_run<T>(ss.m_pid + st, 1u, (const float *)ss.m_orig + st, 0, n2, nx->sink);
+            if (ss.hc_S[ss.sg_cell[s2]] > SEG_GATHER)
+                prefetch_run<T>(ss.m_pid + st, 3u, (const float *)ss.m_v + st, (size_t)ss.m_stride, n2, nx->sink);
+        }
+    }
+    for (uint32_t base = 0; base + first < (uint32_t)n; base += P) {
+        if (base) lds_barrier();
+        lean_round<T, K, F>(base, np2, opaque(n), C, smem, vx, vy, vz, w2, w3, wt, pos, cand, kf, cpid, pid_s, a,
+                            cell, step);
+    }
+    if (nx) __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);
+    const int n3 = opaque(n);
+    uint32_t g[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        g[k] = (uint32_t)(ld_at(ss.m_orig + start, (uint32_t)min((int)threadIdx.x + k * T, n3 - 1)) - lo_c);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if ((int)threadIdx.x + k * T < n3 && !((edge >> k) & 1u)) {
+            st_at((float *)a.v + lo_c, g[k], vx[k]);
+            st_at((float *)a.v + a.n + lo_c, g[k], vy[k]);
+            st_at((float *)a.v + 2 * a.n + lo_c, g[k], vz[k]);
+        }
+    }
+    const int next = nx ? *nx->slot : 0;
+    lds_barrier();   // every thread leaves together; the stores stay in flight
+    return next;
+}
+
 template <typename R, int T, int K, int F>
 __global__ __launch_bounds__(T) void k_seg_collide(CollideArgs a, const int32_t *__restrict__ list,
                                                    SegScratch ss)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t wtot[T / PIC_WAVE];
-    __shared__ int s_item;
+    __shared__ int s_next[3];
     if (gated_off(a)) return;
     const uint32_t count = a.dflags->count[SEG_SLOT];
     if (blockIdx.x >= count) return;   // no work for this workgroup (nor a queue atomic)
-    for (uint32_t item = blockIdx.x; item < count;) {
-        if (threadIdx.x == 0) s_item = (int)queue_take(a.dflags, SEG_SLOT, queue_of(blockIdx.x, gridDim.x), gridDim.x);   // read after the pass's barriers
-        seg_pass<R, T, K, F>(a, list, ss, (int)item, smem, wtot);
-        item = (uint32_t)s_item;
-        __syncthreads();
+    // a queue of the workgroup's own XCD (see xcd_run)
+    const unsigned queue = blockIdx.x % QUEUE_SPLIT;
+    if constexpr (std::is_same<R, float>::value) {
+        __shared__ float sink[PIC_WAVE];
+        if (threadIdx.x == 0) {
+            s_next[1] = (int)queue;
+            s_next[2] = (int)gridDim.x;
+        }
+        const LeanNext nx{s_next, SEG_SLOT, list, count, sink};
+        for (uint32_t item = blockIdx.x; item < count;)
+            item = (uint32_t)lean_seg_pass<T, K, F>(a, list, ss, xcd_run(item, count), smem, wtot, &nx);
+    } else {
+        for (uint32_t item = blockIdx.x; item < count;) {
+            if (threadIdx.x == 0) s_next[0] = (int)queue_take(a.dflags, SEG_SLOT, queue, gridDim.x);   // read after the pass's barriers
+            seg_pass<R, T, K, F>(a, list, ss, (int)xcd_run(item, count), smem, wtot);
+            item = (uint32_t)s_next[0];
+            __syncthreads();
+        }
     }
 }
 
@@ -2083,9 +2260,6 @@ __global__ __launch_bounds__(256) void k_seg_fixup(CollideArgs a, const int32_t 
     R *vx_g = (R *)a.v;
     R *vy_g = vx_g + a.n;
     R *vz_g = vy_g + a.n;
-    const R *mx = (const R *)ss.m_v;
-    const R *my = mx + ss.m_stride;
-    const R *mz = my + ss.m_stride;
     for (uint32_t seg = blockIdx.x * blockDim.x + threadIdx.x; seg < nseg; seg += gridDim.x * blockDim.x) {
         const int32_t sb = ss.bnd_head[seg];
         if (sb < 0) continue;
@@ -2102,8 +2276,9 @@ __global__ __launch_bounds__(256) void k_seg_fixup(CollideArgs a, const int32_t 
         const uint32_t pa = ss.m_pid[sa], pb = ss.m_pid[sb];
         const W4 wa = draw4(a.seed, pa, step, 0u, 0u);
         const W4 wb = draw4(a.seed, pb, step, 0u, 0u);
-        R ax = mx[sa], ay = my[sa], az = mz[sa];
-        R bx = mx[sb], by = my[sb], bz = mz[sb];
+        const int32_t ga = ss.m_orig[sa], gb = ss.m_orig[sb];
+        R ax = vx_g[ga], ay = vy_g[ga], az = vz_g[ga];
+        R bx = vx_g[gb], by = vy_g[gb], bz = vz_g[gb];
         R hx, hy, hz;
         ta_half(ax - bx, ay - by, az - bz, C, wa.z, wa.w, wb.z, hx, hy, hz);
         ax += hx;
@@ -2114,7 +2289,6 @@ __global__ __launch_bounds__(256) void k_seg_fixup(CollideArgs a, const int32_t 
         bz -= hz;
         if (a.mcc_thr && (uint64_t)wa.y < a.mcc_thr) mcc_scatter<R>(ax, ay, az, pa, a.seed, step, a.mass_ratio);
         if (a.mcc_thr && (uint64_t)wb.y < a.mcc_thr) mcc_scatter<R>(bx, by, bz, pb, a.seed, step, a.mass_ratio);
-        const int32_t ga = ss.m_orig[sa], gb = ss.m_orig[sb];
         vx_g[ga] = ax;
         vy_g[ga] = ay;
         vz_g[ga] = az;
@@ -2499,7 +2673,8 @@ __global__ __launch_bounds__(1024) void k_collide_all(CollideArgs a, const int32
         nxt = (uint32_t)s_item;
         lds_barrier();
         if (item < nseg) {
-            seg_pass<R, SG::T, SG::K, F>(a, l4, ss, (int)item, smem, wtot);
+            if constexpr (std::is_same<R, float>::value) lean_seg_pass<SG::T, SG::K, F>(a, l4, ss, item, smem, wtot);
+            else seg_pass<R, SG::T, SG::K, F>(a, l4, ss, (int)item, smem, wtot);
             continue;
         }
         const int cell = order[item - nseg];
@@ -2594,10 +2769,17 @@ int launch_lean64(const CollideArgs &a, const int32_t *list, int cls, int blocks
 SegScratch g_seg;   // set from the workspace before each step's launches
 
 template <typename R, int T, int K, int F>
+constexpr size_t seg_lds_bytes()
+{
+    if constexpr (std::is_same<R, float>::value) return lean_lds_bytes<T, K, F>();
+    else return lds_bytes<R>(T * K);
+}
+
+template <typename R, int T, int K, int F>
 int launch_seg_collide(const CollideArgs &a, const int32_t *list, const SegScratch &ss, int blocks,
                        hipStream_t st)
 {
-    const size_t lds = lds_bytes<R>(T * K);
+    const size_t lds = seg_lds_bytes<R, T, K, F>();
     auto kern = k_seg_collide<R, T, K, F>;
     static bool attr_done = false;
     if (!attr_done) {
@@ -2638,10 +2820,10 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
       if (!seg_done && seg_path) {
         seg_done = true;
         const SegScratch &ss = g_seg;
-        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 4), dim3(SEG_CT), 0, st, a, l4, ss);
+        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         typedef SegGeom<R> G;
         hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, st, a, ss, (uint32_t)(G::T * G::K));
-        hipLaunchKernelGGL(k_seg_scatter<R>, dim3(num_cu * 4), dim3(SEG_CT), 0, st, a, l4, ss);
+        hipLaunchKernelGGL(k_seg_scatter<R>, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         HIP_OK(hipGetLastError());
         if ((rc = launch_seg_collide<R, G::T, G::K, F>(a, l4, ss, G::PER_CU * num_cu, st))) return rc;
         hipLaunchKernelGGL(k_seg_fixup<R>, dim3(num_cu), dim3(256), 0, st, a, l4, ss);
@@ -2695,7 +2877,7 @@ constexpr size_t all_lds_bytes()
 {
     typedef Classes<R> CL;
     size_t b = 16 * WAVE_SLICE;
-    const size_t seg = lds_bytes<R>(SegGeom<R>::T * SegGeom<R>::K);
+    const size_t seg = seg_lds_bytes<R, SegGeom<R>::T, SegGeom<R>::K, F>();
     b = seg > b ? seg : b;
     if constexpr (std::is_same<R, float>::value && (F & ~F_MCC) == 0) {
         const size_t l = lean_lds_bytes<1024, CL::K3, F>();
@@ -2719,10 +2901,10 @@ int launch_unified(const CollideArgs &a, const int32_t *lists, int32_t n_cells, 
     const SegScratch &ss = g_seg;
     if (seg_path) {
         ktime_begin(KT_HUGE, st);
-        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 4), dim3(SEG_CT), 0, st, a, l4, ss);
+        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         typedef SegGeom<R> G;
         hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, st, a, ss, (uint32_t)(G::T * G::K));
-        hipLaunchKernelGGL(k_seg_scatter<R>, dim3(num_cu * 4), dim3(SEG_CT), 0, st, a, l4, ss);
+        hipLaunchKernelGGL(k_seg_scatter<R>, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         ktime_end(KT_HUGE, st);
     }
     const int wave_cls = caps.wave ? 0 : -1;

@@ -673,8 +673,9 @@ const HugeScratch &huge_scratch();
 // after another.  Each segment (at most the
 // segment capacity, seg_cap) is sorted and paired in LDS by its own workgroup at its
 // global offset in the cell; the pair that straddles two segments (when a
-// segment starts at an odd position) is done by a fix-up pass.  Members are
-// first copied segment-major into the scratch below.
+// segment starts at an odd position) is done by a fix-up pass.  Ids and
+// slots (with very many segments the velocities too) are first copied
+// segment-major into the scratch below.
 constexpr int SEG_CHUNK = 8192;        // members per counting / scatter work item
 constexpr int SEG_MAX = 4096;          // at most this many segments per cell
 struct SegScratch {

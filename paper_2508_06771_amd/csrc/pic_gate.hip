@@ -37,17 +37,53 @@ __device__ __forceinline__ float bf16r(float x)
 
 // h(s^2) = E[sin^2 Theta] = E[4 d^2 / (1 + d^2)^2], d ~ N(0, s^2).  With
 // E[1/(1 + t z^2)] = sqrt(pi/(2t)) erfcx(1/sqrt(2t)) and h = -4 t d/dt of it:
-// h = 2 sqrt(pi) w (1 + 2 w^2) erfcx(w) - 4 w^2, w = 1 / sqrt(2 t).  Below
-// t = 1e-3 the closed form cancels (relative error ~1e-16 / t), so the
-// asymptotic Gaussian-moment series is used there (next term ~ 2.5e5 t^6,
-// below 1e-10 relative).
-__device__ __noinline__ double h_angle(double t)
+// h = 2 sqrt(pi) w (1 + 2 w^2) erfcx(w) - 4 w^2, w = 1 / sqrt(2 t).  That form
+// cancels for small t (relative error 1e-16 / t^2), so h is evaluated as
+// w / (w + 5/2)^3 times a polynomial in y = (w - 5/2) / (w + 5/2), which maps
+// all w >= 0 to [-1, 1): a Chebyshev fit in 60 digits, truncated where the
+// rest is below 1e-15.  Within 2.5e-15 of h for every w (4e-16 rms up to 10,
+// 1e-15 beyond), where the closed form with a series below t = 1e-3 was off by
+// up to 1.4e-10 (w > 10), 8e-14 (1 < w < 3) and 1e-15 (w < 0.1).
+__constant__ const double H_POLY[27] = {   // from the highest power
+    -0x1.139b93a32c579p-23, -0x1.19e69f397196fp-21, 0x1.23378c199a724p-21, 0x1.3b5c990c019b7p-18,
+    0x1.2de3a71631ac0p-19, -0x1.36ca0b4b76d10p-16, -0x1.e23d17d6644e0p-16, 0x1.0de1ac4243934p-15,
+    0x1.1f0951c4df9d1p-13, 0x1.04c8dd0ddca30p-14, -0x1.a7fbf80d63beap-12, -0x1.7c7c2f80e1bc3p-11,
+    0x1.5fb5ca311a3d1p-11, 0x1.cd71a1dc2e69bp-9, 0x1.9717120942acbp-11, -0x1.be62a09c8632dp-7,
+    -0x1.a7ef318383821p-7, 0x1.a5a2c2ae6b3c4p-5, 0x1.355dc3fd957c4p-4, -0x1.d2dcc2775a1efp-3,
+    -0x1.491374b305af2p-2, 0x1.4f3f34d7b29d1p+0, 0x1.6fe64817992bcp-2, -0x1.f22c40739c15ep+2,
+    0x1.18ae5e4c3a658p+4, -0x1.408701148f3d3p+4, 0x1.619c914713ac8p+3,
+};
+__device__ __forceinline__ double h_angle(double w)
 {
-    if (t < 1e-3) {
-        return t * (4.0 + t * (-24.0 + t * (180.0 + t * (-1680.0 + t * 18900.0))));
+    // read through a pointer the compiler cannot see through: the coefficients
+    // come from the scalar cache where they are used (kept in vector registers
+    // they cost 54 of them)
+    const double *c = H_POLY;
+    asm volatile("" : "+s"(c));
+    const double r = m64_rcp(w + 2.5), y = __builtin_fma(-5.0, r, 1.0);
+    double p = c[0];
+#pragma unroll
+    for (int i = 1; i < 27; ++i) p = __builtin_fma(p, y, c[i]);
+    return p * (w * r) * (r * r);
+}
+
+// h of a pair with |u|^2 = uu > 0, s^2 = t = C / |u|^3; c2 = 1 / (2 C), so that
+// 1 / (2 t) = c2 |u|^3.  Where the short square roots do not cover the
+// arguments (and for a C that is not positive) the general functions, and the
+// leading terms in t where w is beyond any use.
+__device__ __forceinline__ double h_pair(double uu, double C, double c2)
+{
+    double w;
+    if (uu > 0x1p-80 && uu < 0x1p80 && C > 0x1p-100 && C < 0x1p100) {
+        double r;
+        const double um = m64_sqrt(uu, r);
+        w = m64_sqrt(uu * um * c2, r);
+    } else {
+        const double t = C / (uu * sqrt(uu));
+        if (!(t >= 1e-12)) return t * (4.0 - 24.0 * t);
+        w = 1.0 / sqrt(2.0 * t);
     }
-    const double w = 1.0 / sqrt(2.0 * t);
-    return 2.0 * sqrt(PI_D) * w * (1.0 + 2.0 * w * w) * erfcx(w) - 4.0 * w * w;
+    return h_angle(w);
 }
 
 // Eight features from the raw sums m[0..13] (layout of pic_cell_moments).
@@ -479,13 +515,15 @@ __global__ __launch_bounds__(256) void k_gate_mfma(GateArgs a)
 
 // ------------------------------------------------------------ relaxation label
 // The evaluated cells are first split by size (k_relax_classify).  Cells of
-// at most RELAX_LDS_CAP members: one workgroup per (cell, replica) sorts the
-// replica's keys in LDS and sums the pair terms 1/4 h(s^2) (|u|^2 I - 3 u u^T)
-// into part[]; k_relax_finish adds the replicas in order and normalises.
+// at most RELAX_LDS_CAP members: one workgroup per item of a cell and some of
+// its replicas sorts each replica's keys in LDS and sums the pair terms
+// 1/4 h(s^2) (|u|^2 I - 3 u u^T) into the item's first place of part[] (the
+// others are zero); k_relax_finish adds the replicas in order and normalises.
 // Larger cells take k_relax below.
 constexpr int RELAX_T0 = 256, RELAX_K0 = 8;      // <= 2048 members
 constexpr int RELAX_T1 = 1024, RELAX_K1 = 10;    // <= 10240 members
 constexpr int RELAX_LDS_CAP = RELAX_T1 * RELAX_K1;
+constexpr uint32_t RELAX_REPS = 8;               // replicas of one cell per work item, at most
 constexpr int RELAX_CLASSIFY_T = 512;            // class counts per pass fit 10 bits
 
 __device__ __forceinline__ bool relax_off(const RelaxArgs &a)
@@ -533,135 +571,161 @@ __global__ __launch_bounds__(RELAX_CLASSIFY_T) void k_relax_classify(RelaxArgs a
     if (threadIdx.x < 3) a.cls_count[threadIdx.x] = base[threadIdx.x];
 }
 
+// LDS of one replica: the sort's, then the velocities at their sorted
+// positions, component by component, in rounds of P positions (the whole cell
+// but for the largest binary64 ones).
 template <typename R, int T, int K>
-__global__ __launch_bounds__(T) void k_relax_lds(RelaxArgs a, int cls)
+struct RelaxGeom {
+    static constexpr uint32_t CAP = T * K;
+    static constexpr uint32_t FIT = (uint32_t)((LEAN_LDS_LIMIT - 1024) / (3 * sizeof(R))) & ~63u;
+    static constexpr uint32_t P = CAP < FIT ? CAP : FIT;
+    static constexpr size_t REC = (size_t)P * 3 * sizeof(R);
+    static constexpr size_t BYTES = REC > LeanGeom<T, K>::SORT_BYTES ? REC : LeanGeom<T, K>::SORT_BYTES;
+};
+
+// A work item is some replicas of one cell, whose members stay in registers:
+// each replica sorts (see lean_rank), posts the velocities at their positions
+// and adds its pairs to the item's sums.  Bound by the sort (LDS operations and
+// barriers on 16 waves a CU; the registers do not allow more): 2,048 cells of
+// 2,000 members with 8 replicas 248 us, of 500 101 us.  One replica an item,
+// velocities gathered from memory by sorted index (six scattered loads a pair)
+// and the closed form of h on the library's erfcx took 335 and 152 us.
+template <typename R, int T, int K>
+__global__ __launch_bounds__(T, T >= 1024 || sizeof(R) == 4 ? 4 : 1) void k_relax_lds(RelaxArgs a, int cls)
 {
-    constexpr int CAP = T * K;
-    constexpr int PK = (CAP / 2 + T - 1) / T;    // pairs per thread
+    typedef RelaxGeom<R, T, K> G;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[8 * (T / PIC_WAVE)];
     __shared__ uint32_t wtot[T / PIC_WAVE];
     if (relax_off(a)) return;
-    const uint32_t reps = (uint32_t)a.replicas;
-    const uint32_t items = a.cls_count[cls] * reps;
+    const uint32_t reps = (uint32_t)a.replicas, cells = a.cls_count[cls];
+    // replicas per item: as many as leave every workgroup two items
+    const uint32_t per = min(RELAX_REPS, max(1u, cells * reps / (2u * gridDim.x)));
+    const uint32_t parts = (reps + per - 1) / per;
+    const uint32_t items = cells * parts;
     const int32_t *mine = a.cls_list + (int64_t)cls * a.cap;
     const uint32_t step = (uint32_t)(a.step_dev ? *a.step_dev : a.step);
-    const SortLDS<T, CAP> L(smem);
+    R *px = (R *)smem, *py = px + G::P, *pz = py + G::P;
     for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const uint32_t which = (uint32_t)mine[item / reps], rep = item % reps;
+        const uint32_t which = (uint32_t)mine[item / parts], r0 = item % parts * per;
         const int cell = relax_cell(a, which);
         const int lo = a.cell_start[cell];
         const int n = a.cell_start[cell + 1] - lo;
+        if (n < 2 || n > (int)G::CAP) continue;   // the same for the whole workgroup
+        const uint32_t *pid_c = a.pid + lo;
+        const R *v = (const R *)a.v + lo;
+        uint32_t pid[K];
+        R vx[K], vy[K], vz[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) pid[k] = pid_c[min((int)threadIdx.x + k * T, n - 1)];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int i = min((int)threadIdx.x + k * T, n - 1);
+            vx[k] = v[i];
+            vy[k] = v[a.n + i];
+            vz[k] = v[2 * a.n + i];
+        }
+        const double dens = a.density ? a.density[cell] : 1.0;
+        const double dts = a.dt_scale ? a.dt_scale[cell] : 1.0;
+        const double C = 8.0 * PI_D * dens * a.lnL * a.dt * dts;
+        const double c2 = 0.5 / C;
+        // the cell's temperature waits for k_relax_finish in the cell's result
+        if (r0 == 0) {
+            double s[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if ((int)threadIdx.x + k * T < n) {
+                    const double x = vx[k], y = vy[k], z = vz[k];
+                    s[0] += x;
+                    s[1] += y;
+                    s[2] += z;
+                    s[3] += x * x + y * y + z * z;
+                }
+            block_sum<4>(s, red);
+            const double N = (double)n;
+            if (threadIdx.x == 0)
+                a.r_out[cell] = (s[3] / N - (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) / (N * N)) / 3.0;
+        }
+        const uint32_t bits = sort_bits(n), r1 = min(r0 + per, reps);
         double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // xx yy zz xy xz yz
-        if (n >= 2 && n <= CAP) {
-            const uint32_t *pid_c = a.pid + lo;
-            const uint32_t bits = sort_bits(n);
-            uint32_t pos[K];
-            // the pids are loaded before any is used (pos holds them until
-            // the keys are counted), so the loads are in flight together
+        for (uint32_t rep = r0; rep < r1; ++rep) {
+            uint32_t key[K], pos[K];
+            lean_clear<T, K, true>((uint32_t *)smem, bits);
+            lds_barrier();
+            const int n1 = opaque(n);
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int i = threadIdx.x + k * T;
-                if (i < n) pos[k] = pid_c[i];
-            }
-            L.clear();
-            __syncthreads();
+            for (int k = 0; k < K; ++k)
+                if ((int)threadIdx.x + k * T < n1) {
+                    // (kept from computing the first round of every replica's
+                    // calls ahead, which takes 16 registers and more)
+                    asm volatile("" : "+v"(pid[k]));
+                    key[k] = draw4(a.seed, pid[k], step, 3u, rep).x;
+                    pos[k] = atomicAdd((uint32_t *)smem + (key[k] >> (32u - bits)), 1u);
+                }
+            lean_rank<T, K>(n, bits, pid_c, smem, wtot, key, pos);
+            for (uint32_t base = 0; base < (uint32_t)n; base += G::P) {
+                lds_barrier();   // the sort's memory, or the last round's, becomes this round's
+                const int n2 = opaque(n);
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int i = threadIdx.x + k * T;
-                if (i < n) pos[k] = L.count(i, draw4(a.seed, pos[k], step, 3u, rep).x, bits);
-            }
-            __syncthreads();
-            rank_in_lds<T, K, CAP>(pos, n, bits, L, pid_c, wtot);
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int i = threadIdx.x + k * T;
-                if (i < n) L.lst[pos[k]] = (uint16_t)i;
-            }
-            __syncthreads();
-            const R *vx = (const R *)a.v + lo;
-            const R *vy = (const R *)a.v + a.n + lo;
-            const R *vz = (const R *)a.v + 2 * a.n + lo;
-            const double dens = a.density ? a.density[cell] : 1.0;
-            const double dts = a.dt_scale ? a.dt_scale[cell] : 1.0;
-            const double C = 8.0 * PI_D * dens * a.lnL * a.dt * dts;
-            // all of the thread's pairs are gathered before any is evaluated,
-            // so their loads are in flight together
-            double ux[PK], uy[PK], uz[PK];
-#pragma unroll
-            for (int k = 0; k < PK; ++k) {
-                const int q = threadIdx.x + k * T;
-                ux[k] = uy[k] = uz[k] = 0.0;
-                if (q < n / 2) {
-                    const int ia = L.lst[2 * q], ib = L.lst[2 * q + 1];
-                    ux[k] = (double)vx[ia] - (double)vx[ib];
-                    uy[k] = (double)vy[ia] - (double)vy[ib];
-                    uz[k] = (double)vz[ia] - (double)vz[ib];
+                for (int k = 0; k < K; ++k) {
+                    const uint32_t q = pos[k] - base;
+                    if ((int)threadIdx.x + k * T < n2 && q < G::P) {
+                        px[q] = vx[k];
+                        py[q] = vy[k];
+                        pz[q] = vz[k];
+                    }
+                }
+                lds_barrier();
+                const uint32_t m = min(G::P, (uint32_t)n - base) / 2u;
+#pragma unroll 1
+                for (uint32_t q = threadIdx.x; q < m; q += T) {
+                    const double ux = (double)px[2 * q] - (double)px[2 * q + 1];
+                    const double uy = (double)py[2 * q] - (double)py[2 * q + 1];
+                    const double uz = (double)pz[2 * q] - (double)pz[2 * q + 1];
+                    const double uu = ux * ux + uy * uy + uz * uz;
+                    if (uu == 0.0) continue;
+                    const double hq = 0.25 * h_pair(uu, C, c2);
+                    acc[0] += hq * (uu - 3.0 * ux * ux);
+                    acc[1] += hq * (uu - 3.0 * uy * uy);
+                    acc[2] += hq * (uu - 3.0 * uz * uz);
+                    acc[3] += hq * (-3.0 * ux * uy);
+                    acc[4] += hq * (-3.0 * ux * uz);
+                    acc[5] += hq * (-3.0 * uy * uz);
                 }
             }
-#pragma unroll
-            for (int k = 0; k < PK; ++k) {
-                const double uu = ux[k] * ux[k] + uy[k] * uy[k] + uz[k] * uz[k];
-                if (uu == 0.0) continue;   // also the slots past the last pair
-                const double hq = 0.25 * h_angle(C / (uu * sqrt(uu)));
-                acc[0] += hq * (uu - 3.0 * ux[k] * ux[k]);
-                acc[1] += hq * (uu - 3.0 * uy[k] * uy[k]);
-                acc[2] += hq * (uu - 3.0 * uz[k] * uz[k]);
-                acc[3] += hq * (-3.0 * ux[k] * uy[k]);
-                acc[4] += hq * (-3.0 * ux[k] * uz[k]);
-                acc[5] += hq * (-3.0 * uy[k] * uz[k]);
-            }
+            lds_barrier();   // the next replica reuses the LDS
         }
-        // its barriers also end this item's use of LDS
+        // one sum for the item's replicas, in the first one's place
         const double t = block_sum_scatter<8>(acc, red);
-        if (threadIdx.x < 6) a.part[((size_t)which * reps + rep) * 6 + threadIdx.x] = t;
+        double *part = a.part + ((size_t)which * reps + r0) * 6;
+        if (threadIdx.x < 6 * (r1 - r0)) part[threadIdx.x] = threadIdx.x < 6 ? t : 0.0;
     }
 }
 
-// One workgroup per listed cell of at most RELAX_LDS_CAP members: the cell's
-// temperature, the replica sums in replica order, r.
-template <typename R>
+// One thread per listed cell of at most RELAX_LDS_CAP members: the replica
+// sums in replica order over the cell's temperature (left in r_out).
 __global__ __launch_bounds__(256) void k_relax_finish(RelaxArgs a)
 {
-    __shared__ double red[5 * 4];
-    if (a.dflags && (a.dflags->range_err || (a.assume_sorted && a.dflags->unsorted))) return;
+    if (relax_off(a)) return;
     const uint32_t count = a.count_dev ? *a.count_dev : (uint32_t)a.count;
-    for (uint32_t which = blockIdx.x; which < count; which += gridDim.x) {
-        const int cell = a.list ? a.list[which] : (int)which;
-        const int lo = a.cell_start[cell];
-        const int n = a.cell_start[cell + 1] - lo;
+    for (uint32_t which = blockIdx.x * blockDim.x + threadIdx.x; which < count; which += gridDim.x * blockDim.x) {
+        const int cell = relax_cell(a, which);
+        const int n = a.cell_start[cell + 1] - a.cell_start[cell];
         if (n > RELAX_LDS_CAP) continue;
         if (n < 2) {
-            if (threadIdx.x == 0) a.r_out[cell] = 0.0;
-            __syncthreads();
+            a.r_out[cell] = 0.0;
             continue;
         }
-        const R *vx = (const R *)a.v + lo;
-        const R *vy = (const R *)a.v + a.n + lo;
-        const R *vz = (const R *)a.v + 2 * a.n + lo;
-        double s5[5] = {0, 0, 0, 0, 0};
-        for (int i = threadIdx.x; i < n; i += blockDim.x) {
-            const double x = vx[i], y = vy[i], z = vz[i];
-            s5[1] += x;
-            s5[2] += y;
-            s5[3] += z;
-            s5[4] += x * x + y * y + z * z;
-        }
-        block_sum<5>(s5, red);
-        if (threadIdx.x == 0) {
-            const double N = (double)n;
-            const double T = (s5[4] / N - (s5[1] * s5[1] + s5[2] * s5[2] + s5[3] * s5[3]) / (N * N)) / 3.0;
-            double acc[6] = {0, 0, 0, 0, 0, 0};
-            const double *pc = a.part + (size_t)which * a.replicas * 6;
-            for (int rep = 0; rep < a.replicas; ++rep)
-                for (int c = 0; c < 6; ++c) acc[c] += pc[rep * 6 + c];
-            const double K = (double)a.replicas;
-            double f2 = 0.0;
-            for (int c = 0; c < 3; ++c) f2 += (acc[c] / K) * (acc[c] / K);
-            for (int c = 3; c < 6; ++c) f2 += 2.0 * (acc[c] / K) * (acc[c] / K);
-            a.r_out[cell] = T > 0.0 ? sqrt(f2) / (N * T) : 0.0;
-        }
-        __syncthreads();
+        const double N = (double)n, T = a.r_out[cell];
+        double acc[6] = {0, 0, 0, 0, 0, 0};
+        const double *pc = a.part + (size_t)which * a.replicas * 6;
+        for (int rep = 0; rep < a.replicas; ++rep)
+            for (int c = 0; c < 6; ++c) acc[c] += pc[rep * 6 + c];
+        const double K = (double)a.replicas;
+        double f2 = 0.0;
+        for (int c = 0; c < 3; ++c) f2 += (acc[c] / K) * (acc[c] / K);
+        for (int c = 3; c < 6; ++c) f2 += 2.0 * (acc[c] / K) * (acc[c] / K);
+        a.r_out[cell] = T > 0.0 ? sqrt(f2) / (N * T) : 0.0;
     }
 }
 
@@ -697,7 +761,7 @@ __global__ __launch_bounds__(1024) void k_relax(RelaxArgs a, HugeScratch hs)
         const double T = (s5[4] / N - (s5[1] * s5[1] + s5[2] * s5[2] + s5[3] * s5[3]) / (N * N)) / 3.0;
         const double dens = a.density ? a.density[cell] : 1.0;
         const double dts = a.dt_scale ? a.dt_scale[cell] : 1.0;
-        const double C = 8.0 * PI_D * dens * a.lnL * a.dt * dts;
+        const double C = 8.0 * PI_D * dens * a.lnL * a.dt * dts, c2 = 0.5 / C;
         double acc[6] = {0, 0, 0, 0, 0, 0};   // xx yy zz xy xz yz
         for (int rep = 0; rep < a.replicas; ++rep) {
             for (int i = threadIdx.x; i < n; i += blockDim.x)
@@ -711,7 +775,7 @@ __global__ __launch_bounds__(1024) void k_relax(RelaxArgs a, HugeScratch hs)
                 const double uz = (double)vz[ia] - (double)vz[ib];
                 const double uu = ux * ux + uy * uy + uz * uz;
                 if (uu == 0.0) continue;
-                const double hq = 0.25 * h_angle(C / (uu * sqrt(uu)));
+                const double hq = 0.25 * h_pair(uu, C, c2);
                 acc[0] += hq * (uu - 3.0 * ux * ux);
                 acc[1] += hq * (uu - 3.0 * uy * uy);
                 acc[2] += hq * (uu - 3.0 * uz * uz);
@@ -1206,7 +1270,7 @@ size_t relax_part_bytes(int64_t count, int replicas)
 template <typename R, int T, int K>
 static int launch_relax_lds(const RelaxArgs &a, int cls, int blocks, hipStream_t st)
 {
-    const size_t lds = sort_bytes(T * K);
+    constexpr size_t lds = RelaxGeom<R, T, K>::BYTES;
     auto kern = k_relax_lds<R, T, K>;
     static bool attr_done = false;
     if (!attr_done) {
@@ -1228,10 +1292,10 @@ static int launch_relax_t(const RelaxArgs &a0, int num_cu, hipStream_t st)
     a.cls_list = (int32_t *)(a.part + (size_t)a.cap * a.replicas * 6);
     a.cls_count = (uint32_t *)(a.cls_list + 3 * (size_t)a.cap);
     hipLaunchKernelGGL(k_relax_classify, dim3(1), dim3(RELAX_CLASSIFY_T), 0, st, a);
-    if ((rc = launch_relax_lds<R, RELAX_T0, RELAX_K0>(a, 0, num_cu * 6, st))) return rc;
+    if ((rc = launch_relax_lds<R, RELAX_T0, RELAX_K0>(a, 0, num_cu * 4, st))) return rc;
     if ((rc = launch_relax_lds<R, RELAX_T1, RELAX_K1>(a, 1, num_cu, st))) return rc;
     hipLaunchKernelGGL(k_relax<R>, dim3(num_cu), dim3(1024), 0, st, a, huge_scratch());
-    hipLaunchKernelGGL(k_relax_finish<R>, dim3(num_cu * 4), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_relax_finish, dim3(num_cu), dim3(256), 0, st, a);
     HIP_OK(hipGetLastError());
     return PIC_OK;
 }

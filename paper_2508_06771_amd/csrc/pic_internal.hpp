@@ -666,6 +666,192 @@ struct HugeScratch {
 };
 const HugeScratch &huge_scratch();
 
+// ------------------------------------------------------------ lean sort
+// The counting sort of the lean passes and of the relaxation label: bucket
+// counters of whole words, nb = 2^bits >= n buckets (half a member to one per
+// bucket), so that a member ranks itself among a few keys.
+// Exclusive scan in place of the nb (a power of two) bucket counters, with
+// cnt[nb] = total.  Thread t takes the contiguous run of per = nb / T
+// counters starting at t per (one counter, or none, when nb < T): it sums
+// them, the run totals are scanned across the wave (DPP) and the waves'
+// totals added in order, then it writes its run's starts.  Contains the
+// barriers.
+template <int T, int PERMAX>
+__device__ __forceinline__ void lds_excl_scan_runs(uint32_t *cnt, uint32_t nb, uint32_t *wtot)
+{
+    constexpr int NW = T / PIC_WAVE;
+    const uint32_t lane = threadIdx.x & (PIC_WAVE - 1), wid = threadIdx.x / PIC_WAVE;
+    const uint32_t per = nb >= (uint32_t)T ? nb / (uint32_t)T : (threadIdx.x < nb ? 1u : 0u);
+    uint32_t *run = cnt + threadIdx.x * per;
+    // the run is read twice (its sum, then its starts): no registers held
+    // across the barrier
+    uint32_t s = 0;
+    if (PERMAX >= 4 && per >= 4u) {
+#pragma unroll
+        for (int c = 0; c < PERMAX; c += 4)
+            if ((uint32_t)c < per) {
+                const uint4 q = *(const uint4 *)(run + c);
+                s += (q.x + q.y) + (q.z + q.w);
+            }
+    } else {
+#pragma unroll
+        for (int c = 0; c < (PERMAX < 4 ? PERMAX : 4); ++c)
+            if ((uint32_t)c < per) s += run[c];
+    }
+    const uint32_t inc = wave_incl_scan_dpp(s);
+    if (lane == PIC_WAVE - 1) wtot[wid] = inc;
+    lds_barrier();
+    uint32_t off = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const uint32_t t = wtot[w];
+        off += (uint32_t)w < wid ? t : 0u;
+        tot += t;
+    }
+    uint32_t r = off + inc - s;
+    if (PERMAX >= 4 && per >= 4u) {
+#pragma unroll
+        for (int c = 0; c < PERMAX; c += 4)
+            if ((uint32_t)c < per) {
+                const uint4 x = *(const uint4 *)(run + c);
+                uint4 q;
+                q.x = r;
+                q.y = q.x + x.x;
+                q.z = q.y + x.y;
+                q.w = q.z + x.z;
+                r = q.w + x.w;
+                *(uint4 *)(run + c) = q;
+            }
+    } else {
+#pragma unroll
+        for (int c = 0; c < (PERMAX < 4 ? PERMAX : 4); ++c)
+            if ((uint32_t)c < per) {
+                const uint32_t x = run[c];
+                run[c] = r;
+                r += x;
+            }
+    }
+    if (threadIdx.x == 0) cnt[nb] = tot;
+    lds_barrier();
+}
+
+template <int T, int K>
+struct LeanGeom {
+    static constexpr int CAP = T * K;
+    static constexpr int NBMAX = (int)next_pow2((uint32_t)CAP);
+    static constexpr int PERMAX = NBMAX >= T ? NBMAX / T : 1;   // counters per thread
+    static constexpr size_t CNT_WORDS = (size_t)NBMAX + 4;      // counters, starts, end
+    static constexpr size_t SORT_BYTES = CNT_WORDS * 4 + ((size_t)CAP + 4) * 4 + (size_t)CAP * 2;
+};
+
+// The member count as a value the compiler cannot see through: each phase
+// tests its members against its own copy, so the per-member masks are not
+// kept live (in scalar registers) from one phase to the next.
+__device__ __forceinline__ int opaque(int n)
+{
+    asm volatile("" : "+s"(n));
+    return n;
+}
+
+// Dynamic LDS the lean passes may use: a whole CU's for the 1,024-thread ones
+// (their static part is below 512 bytes, with the cell's sums below 3 KB), half
+// of it for the 512-thread ones, so that two workgroups fit on a CU.
+constexpr size_t LEAN_LDS_LIMIT = 160 * 1024 - 512;
+
+// The 2^bits counters cleared, with CLEAR2 two at a time (8-byte writes).
+template <int T, int K, bool CLEAR2>
+__device__ __forceinline__ void lean_clear(uint32_t *cnt, uint32_t bits)
+{
+    typedef LeanGeom<T, K> G;
+    const uint32_t nb = 1u << bits;
+    const uint32_t per = nb >= (uint32_t)T ? nb / (uint32_t)T : 1u;
+    if (CLEAR2 && G::PERMAX >= 2 && per >= 2u) {
+#pragma unroll
+        for (int q = 0; q < G::PERMAX / 2; ++q)
+            if ((uint32_t)q < per / 2u) *(uint2 *)(cnt + 2 * (threadIdx.x + q * T)) = make_uint2(0u, 0u);
+    } else {
+#pragma unroll
+        for (int q = 0; q < G::PERMAX; ++q)
+            if ((uint32_t)q < per && threadIdx.x + q * T < nb) cnt[threadIdx.x + q * T] = 0u;
+    }
+}
+
+// The counting sort's second half (n >= 2), after every member i = threadIdx.x
+// + k T has its key in key[k] and the arrival rank in its bucket, from the
+// counters at smem, in pos[k]: scan, placement, rank by (key, pid) inside the
+// buckets.  On return pos[k] is the member's position in the sorted order.
+// Contains the barriers (one first); the memory is free after a further one.
+template <int T, int K>
+__device__ __forceinline__ void lean_rank(int n, uint32_t bits, const uint32_t *pid_c, unsigned char *smem,
+                                          uint32_t *wtot, const uint32_t (&key)[K], uint32_t (&pos)[K])
+{
+    typedef LeanGeom<T, K> G;
+    const uint32_t nb = 1u << bits;
+    uint32_t *cnt = (uint32_t *)smem;
+    uint32_t *sk = cnt + G::CNT_WORDS;              // keys in sorted-slot order
+    uint16_t *lst = (uint16_t *)(sk + G::CAP + 4);  // ... and their index in the cell
+    lds_barrier();
+    // bucket starts (cnt[nb] = n)
+    lds_excl_scan_runs<T, G::PERMAX>(cnt, nb, wtot);
+    // slot = bucket start + arrival.  Every member posts its key at its slot
+    // (the three slots past the last hold the largest key), members sharing
+    // their bucket also their index; pos[k] becomes the bucket's start with
+    // its size (15: 15 or more) in the top four bits.
+    const int n2 = opaque(n);
+    if (threadIdx.x < 3) sk[n2 + threadIdx.x] = 0xffffffffu;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int i = threadIdx.x + k * T;
+        if (i < n2) {
+            const uint32_t b = key[k] >> (32u - bits);
+            const uint32_t st = cnt[b], size = cnt[b + 1] - st;
+            const uint32_t slot = st + pos[k];
+            sk[slot] = key[k];
+            if (size > 1u) lst[slot] = (uint16_t)i;
+            pos[k] = st | (min(size, 15u) << 28);
+        }
+    }
+    lds_barrier();
+    // rank by (key, pid) inside the bucket: the keys below this one among
+    // the four slots from the bucket's start (slots of later buckets hold
+    // larger keys) and the rest of the bucket
+    const int n3 = opaque(n);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int i = threadIdx.x + k * T;
+        if (i < n3) {
+            const uint32_t st = pos[k] & 0x0fffffffu;
+            uint32_t size = pos[k] >> 28;
+            uint32_t r = 0, e = 0;
+            uint32_t kj[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) kj[j] = sk[st + j];
+            // one wait for the four reads
+            asm volatile("" ::"v"(kj[0]), "v"(kj[1]), "v"(kj[2]), "v"(kj[3]));
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                r += kj[j] < key[k] ? 1u : 0u;
+                e += kj[j] == key[k] ? 1u : 0u;
+            }
+            if (size > 4u) {
+                if (size == 15u) size = cnt[(key[k] >> (32u - bits)) + 1u] - st;
+                for (uint32_t j = st + 4u; j < st + size; ++j) {
+                    const uint32_t kj = sk[j];
+                    r += kj < key[k] ? 1u : 0u;
+                    e += kj == key[k] ? 1u : 0u;
+                }
+            }
+            if (e > 1u && size > 1u) {
+                // equal keys (rare): the smaller pid comes first
+                const uint32_t pi = pid_c[i];
+                for (uint32_t j = st; j < st + size; ++j)
+                    if (sk[j] == key[k] && pid_c[lst[j]] < pi) ++r;
+            }
+            pos[k] = st + r;
+        }
+    }
+}
+
 // Multi-workgroup path for cells beyond the largest LDS class.  A cell's
 // members are split into S segments by their sort key: segment
 // floor(key S / 2^32), an equal split of the key range.  Since the order is

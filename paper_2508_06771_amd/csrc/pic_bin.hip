@@ -32,6 +32,7 @@ __global__ void k_reset_flags(DevFlags *f)
         f->range_err = 0;
         f->seg_fallback = 0;
         for (int k = 0; k < 4; ++k) f->sort_done[k] = 0;
+        f->seg_done = 0;
     }
     if (threadIdx.x < 8) f->count[threadIdx.x] = 0;
     for (unsigned q = threadIdx.x; q < 8 * QUEUE_SPLIT; q += blockDim.x) f->head[q * QUEUE_LINE] = 0;

@@ -1351,18 +1351,70 @@ __global__ __launch_bounds__(T) void k_collide_lean64(CollideArgs a, const int32
     lean64_pass<T, K, MCC>(a, list[blockIdx.x], smem, wtot, sink);
 }
 
+// After the segments (k_collide_huge): the pairs across segment edges.  The lower member (even position) is the
+// last of the previous non-empty segment of the cell, the upper one the first
+// of this segment; both are still unchanged.  Rotation, the null collisions of
+// both, stores.
+template <typename R>
+__device__ __forceinline__ void seg_fixup(const CollideArgs &a, const int32_t *list, const SegScratch &ss)
+{
+    const uint32_t nseg = a.dflags->count[SEG_SLOT];
+    const uint32_t step = (uint32_t)read_step(a);
+    R *vx_g = (R *)a.v;
+    R *vy_g = vx_g + a.n;
+    R *vz_g = vy_g + a.n;
+    for (uint32_t seg = blockIdx.x * blockDim.x + threadIdx.x; seg < nseg; seg += gridDim.x * blockDim.x) {
+        const int32_t sb = ss.bnd_head[seg];
+        if (sb < 0) continue;
+        const int h = ss.sg_cell[seg];
+        if (ss.hc_fb[h]) continue;
+        int32_t sa = -1;
+        for (int p = (int)seg - 1; p >= ss.hc_seg[h]; --p)
+            if (ss.sg_cnt[p]) {
+                sa = ss.bnd_tail[p];
+                break;
+            }
+        if (sa < 0) continue;   // not reached: an odd offset follows a segment that ends on an even one
+        const R C = (R)cell_C(a, list[h]);
+        const uint32_t pa = ss.m_pid[sa], pb = ss.m_pid[sb];
+        const W4 wa = draw4(a.seed, pa, step, 0u, 0u);
+        const W4 wb = draw4(a.seed, pb, step, 0u, 0u);
+        const int32_t ga = ss.m_orig[sa], gb = ss.m_orig[sb];
+        R ax = vx_g[ga], ay = vy_g[ga], az = vz_g[ga];
+        R bx = vx_g[gb], by = vy_g[gb], bz = vz_g[gb];
+        R hx, hy, hz;
+        ta_half(ax - bx, ay - by, az - bz, C, wa.z, wa.w, wb.z, hx, hy, hz);
+        ax += hx;
+        ay += hy;
+        az += hz;
+        bx -= hx;
+        by -= hy;
+        bz -= hz;
+        if (a.mcc_thr && (uint64_t)wa.y < a.mcc_thr) mcc_scatter<R>(ax, ay, az, pa, a.seed, step, a.mass_ratio);
+        if (a.mcc_thr && (uint64_t)wb.y < a.mcc_thr) mcc_scatter<R>(bx, by, bz, pb, a.seed, step, a.mass_ratio);
+        vx_g[ga] = ax;
+        vy_g[ga] = ay;
+        vz_g[ga] = az;
+        vx_g[gb] = bx;
+        vy_g[gb] = by;
+        vz_g[gb] = bz;
+    }
+}
+
 // ------------------------------------------------------------ huge cells
 // One workgroup per cell; per-particle state in global scratch indexed by the
 // particle's slot, so scratch regions of different cells never overlap.
 template <typename R, bool PAIRS>
 __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int32_t *__restrict__ list,
-                                                       int cls, HugeScratch hs,
+                                                       int cls, HugeScratch hs, SegScratch ss,
                                                        const uint8_t *__restrict__ only)
 {
     __shared__ double red[16 * 16];
     __shared__ uint32_t wtot[16];
     __shared__ int s_item;
     if (gated_off(a)) return;
+    if constexpr (!PAIRS)
+        if (only) seg_fixup<R>(a, list, ss);
     if (only && !a.dflags->seg_fallback) return;   // every cell went the segmented way
     const uint32_t count = a.dflags->count[cls];
     if (blockIdx.x >= count) return;   // no work for this workgroup (nor a queue atomic)
@@ -1598,14 +1650,50 @@ __device__ __forceinline__ SegItem seg_item(const CollideArgs &a, const SegScrat
     return it;
 }
 
+// Each segment's run in the scratch (exclusive scan of the sizes in table
+// order) and the copy cursors, by one workgroup; a cell with a segment beyond
+// cap takes the one-workgroup path.
+__device__ __forceinline__ void seg_scan(const CollideArgs &a, const SegScratch &ss, uint32_t cap, uint32_t *wtot,
+                                         uint32_t *s_tot)
+{
+    const uint32_t nseg = a.dflags->count[SEG_SLOT];
+    uint32_t base = 0;
+    for (uint32_t j0 = 0; j0 < nseg; j0 += SEG_CT) {
+        const uint32_t j = j0 + threadIdx.x;
+        // written by the other workgroups of this launch: read past the caches
+        const uint32_t c =
+            j < nseg ? __hip_atomic_load(&ss.sg_cnt[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        const uint32_t off = block_excl(c, wtot);
+        if (j < nseg) {
+            ss.sg_start[j] = base + off;
+            ss.sg_cur[j] = base + off;
+            if (c > cap) {
+                ss.hc_fb[ss.sg_cell[j]] = 1;
+                a.dflags->seg_fallback = 1;
+            }
+        }
+        if (threadIdx.x == SEG_CT - 1) *s_tot = off + c;
+        __syncthreads();
+        base += *s_tot;
+        __syncthreads();
+    }
+}
+
 // Segment sizes: an LDS histogram per work item, then one global add per
-// non-empty segment.
+// non-empty segment.  The workgroup that ends last scans them (its counts are
+// read after every other workgroup's adds have completed: each waits for its
+// own before it reports).  With the edge pairs done in k_collide_huge the
+// path is four launches instead of six, about 2.7 us each where it has nothing
+// to do.
 __global__ __launch_bounds__(SEG_CT) void k_seg_count(CollideArgs a, const int32_t *__restrict__ list,
-                                                      SegScratch ss)
+                                                      SegScratch ss, uint32_t cap)
 {
     __shared__ uint32_t hist[SEG_MAX];
+    __shared__ uint32_t wtot[SEG_CT / PIC_WAVE];
+    __shared__ uint32_t s_tot;
     if (gated_off(a)) return;
     const uint32_t items = a.dflags->count[CHUNK_SLOT];
+    if (blockIdx.x >= items) return;
     const uint32_t step = (uint32_t)read_step(a);
     for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
         const SegItem it = seg_item(a, ss, list, item);
@@ -1626,35 +1714,14 @@ __global__ __launch_bounds__(SEG_CT) void k_seg_count(CollideArgs a, const int32
             if (hist[q]) atomicAdd(&ss.sg_cnt[sb + q], hist[q]);
         __syncthreads();
     }
-}
-
-// One workgroup: each segment's run in the scratch (exclusive scan of the
-// sizes in table order) and the copy cursors; a cell with a segment beyond
-// cap takes the one-workgroup path.
-__global__ __launch_bounds__(1024) void k_seg_scan(CollideArgs a, SegScratch ss, uint32_t cap)
-{
-    __shared__ uint32_t wtot[16];
-    __shared__ uint32_t s_tot;
-    if (gated_off(a)) return;
-    const uint32_t nseg = a.dflags->count[SEG_SLOT];
-    uint32_t base = 0;
-    for (uint32_t j0 = 0; j0 < nseg; j0 += 1024) {
-        const uint32_t j = j0 + threadIdx.x;
-        const uint32_t c = j < nseg ? ss.sg_cnt[j] : 0u;
-        const uint32_t off = block_excl(c, wtot);
-        if (j < nseg) {
-            ss.sg_start[j] = base + off;
-            ss.sg_cur[j] = base + off;
-            if (c > cap) {
-                ss.hc_fb[ss.sg_cell[j]] = 1;
-                a.dflags->seg_fallback = 1;
-            }
-        }
-        if (threadIdx.x == 1023) s_tot = off + c;
-        __syncthreads();
-        base += s_tot;
-        __syncthreads();
-    }
+    __builtin_amdgcn_s_waitcnt(WAIT_VMCNT0);   // this wave's adds have completed
+    __syncthreads();
+    if (threadIdx.x == 0)
+        s_tot = __hip_atomic_fetch_add(&a.dflags->seg_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const bool last = s_tot + 1u == min(gridDim.x, items);
+    __syncthreads();
+    if (last) seg_scan(a, ss, cap, wtot, &s_tot);
 }
 
 // Members to their segment's run: each member's arrival rank in its segment
@@ -1732,7 +1799,7 @@ static_assert(SEG_MAX <= 1 << 16 && SEG_CHUNK <= 1 << 16, "segment and rank shar
 // bucket them) and pid; local
 // position q is position off + q of the cell.  The cell's pairs (2i, 2i + 1)
 // inside the segment collide here as in the cell pass; a member whose
-// partner lies in a neighbouring segment is recorded for k_seg_fixup and left
+// partner lies in a neighbouring segment is recorded for seg_fixup and left
 // unchanged (its null collision too).
 template <typename R, int T, int K, int F>
 __device__ __forceinline__ void seg_pass(const CollideArgs &a, const int32_t *list, const SegScratch &ss, int seg,
@@ -2083,58 +2150,6 @@ __global__ __launch_bounds__(T) void k_seg_collide(CollideArgs a, const int32_t 
             item = (uint32_t)s_next[0];
             __syncthreads();
         }
-    }
-}
-
-// The pairs across segment edges: the lower member (even position) is the
-// last of the previous non-empty segment of the cell, the upper one the first
-// of this segment; both are still unchanged.  Rotation, the null collisions of
-// both, stores.
-template <typename R>
-__global__ __launch_bounds__(256) void k_seg_fixup(CollideArgs a, const int32_t *__restrict__ list,
-                                                   SegScratch ss)
-{
-    if (gated_off(a)) return;
-    const uint32_t nseg = a.dflags->count[SEG_SLOT];
-    const uint32_t step = (uint32_t)read_step(a);
-    R *vx_g = (R *)a.v;
-    R *vy_g = vx_g + a.n;
-    R *vz_g = vy_g + a.n;
-    for (uint32_t seg = blockIdx.x * blockDim.x + threadIdx.x; seg < nseg; seg += gridDim.x * blockDim.x) {
-        const int32_t sb = ss.bnd_head[seg];
-        if (sb < 0) continue;
-        const int h = ss.sg_cell[seg];
-        if (ss.hc_fb[h]) continue;
-        int32_t sa = -1;
-        for (int p = (int)seg - 1; p >= ss.hc_seg[h]; --p)
-            if (ss.sg_cnt[p]) {
-                sa = ss.bnd_tail[p];
-                break;
-            }
-        if (sa < 0) continue;   // not reached: an odd offset follows a segment that ends on an even one
-        const R C = (R)cell_C(a, list[h]);
-        const uint32_t pa = ss.m_pid[sa], pb = ss.m_pid[sb];
-        const W4 wa = draw4(a.seed, pa, step, 0u, 0u);
-        const W4 wb = draw4(a.seed, pb, step, 0u, 0u);
-        const int32_t ga = ss.m_orig[sa], gb = ss.m_orig[sb];
-        R ax = vx_g[ga], ay = vy_g[ga], az = vz_g[ga];
-        R bx = vx_g[gb], by = vy_g[gb], bz = vz_g[gb];
-        R hx, hy, hz;
-        ta_half(ax - bx, ay - by, az - bz, C, wa.z, wa.w, wb.z, hx, hy, hz);
-        ax += hx;
-        ay += hy;
-        az += hz;
-        bx -= hx;
-        by -= hy;
-        bz -= hz;
-        if (a.mcc_thr && (uint64_t)wa.y < a.mcc_thr) mcc_scatter<R>(ax, ay, az, pa, a.seed, step, a.mass_ratio);
-        if (a.mcc_thr && (uint64_t)wb.y < a.mcc_thr) mcc_scatter<R>(bx, by, bz, pb, a.seed, step, a.mass_ratio);
-        vx_g[ga] = ax;
-        vy_g[ga] = ay;
-        vz_g[ga] = az;
-        vx_g[gb] = bx;
-        vy_g[gb] = by;
-        vz_g[gb] = bz;
     }
 }
 
@@ -2660,21 +2675,19 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
       if (!seg_done && seg_path) {
         seg_done = true;
         const SegScratch &ss = g_seg;
-        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         typedef SegGeom<R> G;
-        hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, st, a, ss, (uint32_t)(G::T * G::K));
+        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss, (uint32_t)(G::T * G::K));
         hipLaunchKernelGGL(k_seg_scatter<R>, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         HIP_OK(hipGetLastError());
         if ((rc = launch_seg_collide<R, G::T, G::K, F>(a, l4, ss, G::PER_CU * num_cu, st))) return rc;
-        hipLaunchKernelGGL(k_seg_fixup<R>, dim3(num_cu), dim3(256), 0, st, a, l4, ss);
         // cells the plan could not segment
         hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
-                           hs, (const uint8_t *)ss.hc_fb);
+                           hs, g_seg, (const uint8_t *)ss.hc_fb);
       }
     }
     if (!seg_done)
         hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
-                           hs, (const uint8_t *)nullptr);
+                           hs, g_seg, (const uint8_t *)nullptr);
     if (live & (1u << 4)) ktime_end(KT_HUGE, st);
     HIP_OK(hipGetLastError());
     if (live & (1u << 3)) {
@@ -2741,9 +2754,8 @@ int launch_unified(const CollideArgs &a, const int32_t *lists, int32_t n_cells, 
     const SegScratch &ss = g_seg;
     if (seg_path) {
         ktime_begin(KT_HUGE, st);
-        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         typedef SegGeom<R> G;
-        hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, st, a, ss, (uint32_t)(G::T * G::K));
+        hipLaunchKernelGGL(k_seg_count, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss, (uint32_t)(G::T * G::K));
         hipLaunchKernelGGL(k_seg_scatter<R>, dim3(num_cu * 2), dim3(SEG_CT), 0, st, a, l4, ss);
         ktime_end(KT_HUGE, st);
     }
@@ -2767,11 +2779,10 @@ int launch_unified(const CollideArgs &a, const int32_t *lists, int32_t n_cells, 
     HIP_OK(hipGetLastError());
     ktime_begin(KT_HUGE, st);
     if (seg_path) {
-        hipLaunchKernelGGL(k_seg_fixup<R>, dim3(num_cu), dim3(256), 0, st, a, l4, ss);
-        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs,
+        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs, g_seg,
                            (const uint8_t *)ss.hc_fb);
     } else {
-        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs,
+        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs, g_seg,
                            (const uint8_t *)nullptr);
     }
     ktime_end(KT_HUGE, st);

@@ -29,6 +29,7 @@ struct DevFlags {
     unsigned int count[8];  // work-queue lengths (cells per class)
     unsigned int seg_fallback; // some cell of that class takes the one-workgroup path
     unsigned int sort_done[4];  // workgroups done counting, per re-binning pass
+    unsigned int seg_done;      // ... and of the segment sizes
     unsigned int pad[5];
     // work-queue heads of the persistent kernels (see queue_take)
     unsigned int head[8 * QUEUE_SPLIT * QUEUE_LINE];

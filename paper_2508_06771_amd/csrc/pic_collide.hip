@@ -96,6 +96,7 @@ __device__ __forceinline__ void ta_half_z(float ux, float uy, float uz, float C,
     hz = 0.5f * dz;
 }
 
+template <bool MEM = false>
 __device__ __forceinline__ void ta_half(float ux, float uy, float uz, float C, uint32_t wa2,
                                         uint32_t wa3, uint32_t wb2, float &hx, float &hy,
                                         float &hz)
@@ -103,18 +104,19 @@ __device__ __forceinline__ void ta_half(float ux, float uy, float uz, float C, u
     ta_half_z(ux, uy, uz, C, ta_z(wa2, wa3), wb2, hx, hy, hz);
 }
 
+template <bool MEM = false>   // see m64_ta_half
 __device__ __forceinline__ void ta_half(double ux, double uy, double uz, double C, uint32_t wa2,
                                         uint32_t wa3, uint32_t wb2, double &hx, double &hy,
                                         double &hz)
 {
-    m64_ta_half(ux, uy, uz, C, u01d(wa2), u01d(wa3), u01d(wb2), hx, hy, hz);
+    m64_ta_half<MEM>(ux, uy, uz, C, u01d(wa2), u01d(wa3), u01d(wb2), hx, hy, hz);
 }
 
-template <typename R>
+template <typename R, bool MEM = false>
 __device__ __forceinline__ void mcc_scatter(R &vx, R &vy, R &vz, uint32_t pid, uint64_t seed,
                                             uint32_t step, double mass_ratio)
 {
-    scatter_dir(vx, vy, vz, draw4(seed, pid, step, 1u, 0u), mass_ratio);
+    scatter_dir<MEM>(vx, vy, vz, draw4(seed, pid, step, 1u, 0u), mass_ratio);
 }
 
 __device__ __forceinline__ uint64_t read_step(const CollideArgs &a)
@@ -387,7 +389,7 @@ __device__ __forceinline__ void scatter_regs(const CollideArgs &a, uint32_t cand
                 y = kk == k ? ay : y;
                 z = kk == k ? az : z;
             }
-            mcc_scatter<R>(x, y, z, pid_c[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
+            mcc_scatter<R, (T >= 1024)>(x, y, z, pid_c[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const R ax = vx[k], ay = vy[k], az = vz[k];
@@ -555,7 +557,7 @@ __device__ __forceinline__ void cell_pass(const CollideArgs &a, int cell, unsign
                         hz = -hz;
                     }
                 } else {
-                    ta_half(A.x - B.x, A.y - B.y, A.z - B.z, C, A.w2, w3s[j], B.w2, hx, hy, hz);
+                    ta_half<(T >= 1024)>(A.x - B.x, A.y - B.y, A.z - B.z, C, A.w2, w3s[j], B.w2, hx, hy, hz);
                     if constexpr (WT) weight_rule<R>(wts[2 * j], wts[2 * j + 1], w3b[j], ta, tb);
                 }
                 if (ta) {
@@ -1256,7 +1258,7 @@ __device__ __forceinline__ void lean64_pass(const CollideArgs &a, int cell, unsi
             for (uint32_t j = threadIdx.x; j < m; j += T) {
                 Rec<double> A = rec[2 * j], B = rec[2 * j + 1];
                 double hx, hy, hz;
-                ta_half(A.x - B.x, A.y - B.y, A.z - B.z, C, A.w2, A.pad, B.w2, hx, hy, hz);
+                ta_half<(K > 4)>(A.x - B.x, A.y - B.y, A.z - B.z, C, A.w2, A.pad, B.w2, hx, hy, hz);
                 A.x += hx;
                 A.y += hy;
                 A.z += hz;
@@ -1302,7 +1304,7 @@ __device__ __forceinline__ void lean64_pass(const CollideArgs &a, int cell, unsi
                         const int i = (int)tid + kk * T;
                         const Rec<double> e = rec[pk - base5];
                         double x = e.x, y = e.y, z = e.z;
-                        mcc_scatter<double>(x, y, z, pid_c[i], a.seed, step, a.mass_ratio);
+                        mcc_scatter<double, (K > 4)>(x, y, z, pid_c[i], a.seed, step, a.mass_ratio);
                         st_at(vx_g, (uint32_t)i, x);
                         st_at(vy_g, (uint32_t)i, y);
                         st_at(vz_g, (uint32_t)i, z);
@@ -1327,7 +1329,7 @@ __device__ __forceinline__ void lean64_pass(const CollideArgs &a, int cell, unsi
             const int kk = __builtin_ctz(left);   // at most one such member per cell
             const int i = threadIdx.x + kk * T;
             double x = ld_at(vx_g, (uint32_t)i), y = ld_at(vy_g, (uint32_t)i), z = ld_at(vz_g, (uint32_t)i);
-            mcc_scatter<double>(x, y, z, pid_c[i], a.seed, step, a.mass_ratio);
+            mcc_scatter<double, (K > 4)>(x, y, z, pid_c[i], a.seed, step, a.mass_ratio);
             st_at(vx_g, (uint32_t)i, x);
             st_at(vy_g, (uint32_t)i, y);
             st_at(vz_g, (uint32_t)i, z);
@@ -1911,7 +1913,7 @@ __device__ __forceinline__ void seg_pass(const CollideArgs &a, const int32_t *li
             for (uint32_t j = threadIdx.x; j < m; j += T) {
                 Rec<R> A = rec[2 * j], B = rec[2 * j + 1];
                 R hx, hy, hz;
-                ta_half(A.x - B.x, A.y - B.y, A.z - B.z, C, A.w2, w3s[j], B.w2, hx, hy, hz);
+                ta_half<true>(A.x - B.x, A.y - B.y, A.z - B.z, C, A.w2, w3s[j], B.w2, hx, hy, hz);
                 A.x += hx;
                 A.y += hy;
                 A.z += hz;
@@ -1951,7 +1953,7 @@ __device__ __forceinline__ void seg_pass(const CollideArgs &a, const int32_t *li
                         y = vy[k];
                         z = vz[k];
                     }
-                mcc_scatter<R>(x, y, z, pid_s[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
+                mcc_scatter<R, true>(x, y, z, pid_s[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
 #pragma unroll
                 for (int k = 0; k < K; ++k)
                     if (kk == k) {

@@ -191,6 +191,7 @@ __device__ __forceinline__ T nb_omc(T A, T U)
 // nu = n_n sigma0 sqrt(2) = nu_max, so the real/null test U(w.x) nu_max < nu
 // always passes and is not evaluated.
 // ---------------------------------------------------------------------------
+template <bool MEM = false>
 __device__ __forceinline__ void scatter_dir(float &vx, float &vy, float &vz, const W4 &w,
                                             double mass_ratio)
 {
@@ -211,6 +212,7 @@ __device__ __forceinline__ void scatter_dir(float &vx, float &vy, float &vz, con
     vz = scale * sz;
 }
 
+template <bool MEM = false>   // see m64_sincos
 __device__ __forceinline__ void scatter_dir(double &vx, double &vy, double &vz, const W4 &w,
                                             double mass_ratio)
 {
@@ -218,7 +220,7 @@ __device__ __forceinline__ void scatter_dir(double &vx, double &vy, double &vz, 
     const double ct = 1.0 - 2.0 * u01d(w.y);
     double r, sn, cs;
     const double st = m64_sqrt(1.0 - ct * ct, r);   // U is in (0, 1): at least 2^-22
-    m64_sincos(2.0 * 3.14159265358979323846 * u01d(w.z), sn, cs);
+    m64_sincos<MEM>(2.0 * 3.14159265358979323846 * u01d(w.z), sn, cs);
     const double sx = st * cs, sy = st * sn, sz = ct;
     const double sp = sqrt(vx * vx + vy * vy + vz * vz);
     double scale = sp;

@@ -518,7 +518,7 @@ __global__ __launch_bounds__(256) void k_gate_mfma(GateArgs a)
 // at most RELAX_LDS_CAP members: one workgroup per item of a cell and some of
 // its replicas sorts each replica's keys in LDS and sums the pair terms
 // 1/4 h(s^2) (|u|^2 I - 3 u u^T) into the item's first place of part[] (the
-// others are zero); k_relax_finish adds the replicas in order and normalises.
+// others are zero); relax_finish adds the replicas in order and normalises.
 // Larger cells take k_relax below.
 constexpr int RELAX_T0 = 256, RELAX_K0 = 8;      // <= 2048 members
 constexpr int RELAX_T1 = 1024, RELAX_K1 = 10;    // <= 10240 members
@@ -587,128 +587,148 @@ struct RelaxGeom {
 // each replica sorts (see lean_rank), posts the velocities at their positions
 // and adds its pairs to the item's sums.  Bound by the sort (LDS operations and
 // barriers on 16 waves a CU; the registers do not allow more): 2,048 cells of
-// 2,000 members with 8 replicas 248 us, of 500 101 us.  One replica an item,
+// 2,000 members with 8 replicas 246 us, of 500 88 us.  One replica an item,
 // velocities gathered from memory by sorted index (six scattered loads a pair)
 // and the closed form of h on the library's erfcx took 335 and 152 us.
 template <typename R, int T, int K>
-__global__ __launch_bounds__(T, T >= 1024 || sizeof(R) == 4 ? 4 : 1) void k_relax_lds(RelaxArgs a, int cls)
+__device__ __forceinline__ void relax_item(const RelaxArgs &a, uint32_t which, int cell, int lo, int n, uint32_t r0,
+                                           uint32_t r1, uint32_t step, unsigned char *smem, double *red,
+                                           uint32_t *wtot)
 {
     typedef RelaxGeom<R, T, K> G;
+    const uint32_t reps = (uint32_t)a.replicas;
+    R *px = (R *)smem, *py = px + G::P, *pz = py + G::P;
+    const uint32_t *pid_c = a.pid + lo;
+    const R *v = (const R *)a.v + lo;
+    uint32_t pid[K];
+    R vx[K], vy[K], vz[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) pid[k] = pid_c[min((int)threadIdx.x + k * T, n - 1)];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int i = min((int)threadIdx.x + k * T, n - 1);
+        vx[k] = v[i];
+        vy[k] = v[a.n + i];
+        vz[k] = v[2 * a.n + i];
+    }
+    const double dens = a.density ? a.density[cell] : 1.0;
+    const double dts = a.dt_scale ? a.dt_scale[cell] : 1.0;
+    const double C = 8.0 * PI_D * dens * a.lnL * a.dt * dts;
+    const double c2 = 0.5 / C;
+    // the cell's temperature waits for relax_finish in the cell's result
+    if (r0 == 0) {
+        double s[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if ((int)threadIdx.x + k * T < n) {
+                const double x = vx[k], y = vy[k], z = vz[k];
+                s[0] += x;
+                s[1] += y;
+                s[2] += z;
+                s[3] += x * x + y * y + z * z;
+            }
+        block_sum<4>(s, red);
+        const double N = (double)n;
+        if (threadIdx.x == 0)
+            a.r_out[cell] = (s[3] / N - (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) / (N * N)) / 3.0;
+    }
+    const uint32_t bits = sort_bits(n);
+    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // xx yy zz xy xz yz
+    for (uint32_t rep = r0; rep < r1; ++rep) {
+        uint32_t key[K], pos[K];
+        lean_clear<T, K, true>((uint32_t *)smem, bits);
+        lds_barrier();
+        const int n1 = opaque(n);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if ((int)threadIdx.x + k * T < n1) {
+                // (kept from computing the first round of every replica's
+                // calls ahead, which takes 16 registers and more)
+                asm volatile("" : "+v"(pid[k]));
+                key[k] = draw4(a.seed, pid[k], step, 3u, rep).x;
+                pos[k] = atomicAdd((uint32_t *)smem + (key[k] >> (32u - bits)), 1u);
+            }
+        lean_rank<T, K>(n, bits, pid_c, smem, wtot, key, pos);
+        for (uint32_t base = 0; base < (uint32_t)n; base += G::P) {
+            lds_barrier();   // the sort's memory, or the last round's, becomes this round's
+            const int n2 = opaque(n);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const uint32_t q = pos[k] - base;
+                if ((int)threadIdx.x + k * T < n2 && q < G::P) {
+                    px[q] = vx[k];
+                    py[q] = vy[k];
+                    pz[q] = vz[k];
+                }
+            }
+            lds_barrier();
+            const uint32_t m = min(G::P, (uint32_t)n - base) / 2u;
+#pragma unroll 1
+            for (uint32_t q = threadIdx.x; q < m; q += T) {
+                const double ux = (double)px[2 * q] - (double)px[2 * q + 1];
+                const double uy = (double)py[2 * q] - (double)py[2 * q + 1];
+                const double uz = (double)pz[2 * q] - (double)pz[2 * q + 1];
+                const double uu = ux * ux + uy * uy + uz * uz;
+                if (uu == 0.0) continue;
+                const double hq = 0.25 * h_pair(uu, C, c2);
+                acc[0] += hq * (uu - 3.0 * ux * ux);
+                acc[1] += hq * (uu - 3.0 * uy * uy);
+                acc[2] += hq * (uu - 3.0 * uz * uz);
+                acc[3] += hq * (-3.0 * ux * uy);
+                acc[4] += hq * (-3.0 * ux * uz);
+                acc[5] += hq * (-3.0 * uy * uz);
+            }
+        }
+        lds_barrier();   // the next replica reuses the LDS
+    }
+    // one sum for the item's replicas, in the first one's place
+    const double t = block_sum_scatter<8>(acc, red);
+    double *part = a.part + ((size_t)which * reps + r0) * 6;
+    if (threadIdx.x < 6 * (r1 - r0)) part[threadIdx.x] = threadIdx.x < 6 ? t : 0.0;
+}
+
+template <typename R, int T, int K>
+__global__ __launch_bounds__(T, T >= 1024 || sizeof(R) == 4 ? 4 : 1) void k_relax_lds(RelaxArgs a, int cls)
+{
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double red[8 * (T / PIC_WAVE)];
     __shared__ uint32_t wtot[T / PIC_WAVE];
     if (relax_off(a)) return;
     const uint32_t reps = (uint32_t)a.replicas, cells = a.cls_count[cls];
-    // replicas per item: as many as leave every workgroup two items
-    const uint32_t per = min(RELAX_REPS, max(1u, cells * reps / (2u * gridDim.x)));
+    // replicas per item: where the last workgroup ends soonest, an item's loads
+    // and sums counted as one replica more (160 cells of 9,000 with 8 replicas, on
+    // 256 workgroups: one replica an item 195 us, two 173, five 238)
+    uint32_t per = 1, best = ~0u;
+    for (uint32_t q = 1; q <= min(RELAX_REPS, reps); ++q) {
+        const uint32_t rounds = (cells * ((reps + q - 1) / q) + gridDim.x - 1) / gridDim.x;
+        if (rounds * (q + 1) < best) {
+            best = rounds * (q + 1);
+            per = q;
+        }
+    }
     const uint32_t parts = (reps + per - 1) / per;
     const uint32_t items = cells * parts;
     const int32_t *mine = a.cls_list + (int64_t)cls * a.cap;
     const uint32_t step = (uint32_t)(a.step_dev ? *a.step_dev : a.step);
-    R *px = (R *)smem, *py = px + G::P, *pz = py + G::P;
     for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const uint32_t which = (uint32_t)mine[item / parts], r0 = item % parts * per;
+        const uint32_t which = (uint32_t)mine[item / parts], r0 = item % parts * per, r1 = min(r0 + per, reps);
         const int cell = relax_cell(a, which);
         const int lo = a.cell_start[cell];
         const int n = a.cell_start[cell + 1] - lo;
-        if (n < 2 || n > (int)G::CAP) continue;   // the same for the whole workgroup
-        const uint32_t *pid_c = a.pid + lo;
-        const R *v = (const R *)a.v + lo;
-        uint32_t pid[K];
-        R vx[K], vy[K], vz[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) pid[k] = pid_c[min((int)threadIdx.x + k * T, n - 1)];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int i = min((int)threadIdx.x + k * T, n - 1);
-            vx[k] = v[i];
-            vy[k] = v[a.n + i];
-            vz[k] = v[2 * a.n + i];
-        }
-        const double dens = a.density ? a.density[cell] : 1.0;
-        const double dts = a.dt_scale ? a.dt_scale[cell] : 1.0;
-        const double C = 8.0 * PI_D * dens * a.lnL * a.dt * dts;
-        const double c2 = 0.5 / C;
-        // the cell's temperature waits for k_relax_finish in the cell's result
-        if (r0 == 0) {
-            double s[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                if ((int)threadIdx.x + k * T < n) {
-                    const double x = vx[k], y = vy[k], z = vz[k];
-                    s[0] += x;
-                    s[1] += y;
-                    s[2] += z;
-                    s[3] += x * x + y * y + z * z;
-                }
-            block_sum<4>(s, red);
-            const double N = (double)n;
-            if (threadIdx.x == 0)
-                a.r_out[cell] = (s[3] / N - (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) / (N * N)) / 3.0;
-        }
-        const uint32_t bits = sort_bits(n), r1 = min(r0 + per, reps);
-        double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // xx yy zz xy xz yz
-        for (uint32_t rep = r0; rep < r1; ++rep) {
-            uint32_t key[K], pos[K];
-            lean_clear<T, K, true>((uint32_t *)smem, bits);
-            lds_barrier();
-            const int n1 = opaque(n);
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-                if ((int)threadIdx.x + k * T < n1) {
-                    // (kept from computing the first round of every replica's
-                    // calls ahead, which takes 16 registers and more)
-                    asm volatile("" : "+v"(pid[k]));
-                    key[k] = draw4(a.seed, pid[k], step, 3u, rep).x;
-                    pos[k] = atomicAdd((uint32_t *)smem + (key[k] >> (32u - bits)), 1u);
-                }
-            lean_rank<T, K>(n, bits, pid_c, smem, wtot, key, pos);
-            for (uint32_t base = 0; base < (uint32_t)n; base += G::P) {
-                lds_barrier();   // the sort's memory, or the last round's, becomes this round's
-                const int n2 = opaque(n);
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const uint32_t q = pos[k] - base;
-                    if ((int)threadIdx.x + k * T < n2 && q < G::P) {
-                        px[q] = vx[k];
-                        py[q] = vy[k];
-                        pz[q] = vz[k];
-                    }
-                }
-                lds_barrier();
-                const uint32_t m = min(G::P, (uint32_t)n - base) / 2u;
-#pragma unroll 1
-                for (uint32_t q = threadIdx.x; q < m; q += T) {
-                    const double ux = (double)px[2 * q] - (double)px[2 * q + 1];
-                    const double uy = (double)py[2 * q] - (double)py[2 * q + 1];
-                    const double uz = (double)pz[2 * q] - (double)pz[2 * q + 1];
-                    const double uu = ux * ux + uy * uy + uz * uz;
-                    if (uu == 0.0) continue;
-                    const double hq = 0.25 * h_pair(uu, C, c2);
-                    acc[0] += hq * (uu - 3.0 * ux * ux);
-                    acc[1] += hq * (uu - 3.0 * uy * uy);
-                    acc[2] += hq * (uu - 3.0 * uz * uz);
-                    acc[3] += hq * (-3.0 * ux * uy);
-                    acc[4] += hq * (-3.0 * ux * uz);
-                    acc[5] += hq * (-3.0 * uy * uz);
-                }
-            }
-            lds_barrier();   // the next replica reuses the LDS
-        }
-        // one sum for the item's replicas, in the first one's place
-        const double t = block_sum_scatter<8>(acc, red);
-        double *part = a.part + ((size_t)which * reps + r0) * 6;
-        if (threadIdx.x < 6 * (r1 - r0)) part[threadIdx.x] = threadIdx.x < 6 ? t : 0.0;
+        if (n < 2 || n > T * K) continue;   // the same for the whole workgroup
+        // small cells without the loads and branches of members they lack
+        if (T < 1024 && n <= 2 * T) relax_item<R, T, 2>(a, which, cell, lo, n, r0, r1, step, smem, red, wtot);
+        else relax_item<R, T, K>(a, which, cell, lo, n, r0, r1, step, smem, red, wtot);
     }
 }
 
 // One thread per listed cell of at most RELAX_LDS_CAP members: the replica
 // sums in replica order over the cell's temperature (left in r_out).
-__global__ __launch_bounds__(256) void k_relax_finish(RelaxArgs a)
+__device__ __forceinline__ void relax_finish(const RelaxArgs &a)
 {
-    if (relax_off(a)) return;
     const uint32_t count = a.count_dev ? *a.count_dev : (uint32_t)a.count;
-    for (uint32_t which = blockIdx.x * blockDim.x + threadIdx.x; which < count; which += gridDim.x * blockDim.x) {
+    // neighbouring cells to different workgroups (a few cells would else fill one)
+    for (uint32_t which = threadIdx.x * gridDim.x + blockIdx.x; which < count; which += gridDim.x * blockDim.x) {
         const int cell = relax_cell(a, which);
         const int n = a.cell_start[cell + 1] - a.cell_start[cell];
         if (n > RELAX_LDS_CAP) continue;
@@ -729,7 +749,8 @@ __global__ __launch_bounds__(256) void k_relax_finish(RelaxArgs a)
     }
 }
 
-// Cells above RELAX_LDS_CAP members: one workgroup per listed cell: r = || (1/K) sum_replicas sum_pairs
+// The other cells' labels from their sums (relax_finish), then the cells above
+// RELAX_LDS_CAP members: one workgroup per listed cell: r = || (1/K) sum_replicas sum_pairs
 // 1/4 h(s^2) (|u|^2 I - 3 u u^T) ||_F / (N T), pairs from independent
 // re-pairings (domain 3, c3 = replica); s^2 = 8 pi n lnL dt dt_scale / |u|^3.
 template <typename R>
@@ -738,6 +759,7 @@ __global__ __launch_bounds__(1024) void k_relax(RelaxArgs a, HugeScratch hs)
     __shared__ double red[6 * 16];
     __shared__ uint32_t wtot[16];
     if (relax_off(a)) return;
+    relax_finish(a);
     const uint64_t step = a.step_dev ? *a.step_dev : a.step;
     const R *vx = (const R *)a.v;
     const R *vy = vx + a.n;
@@ -1295,7 +1317,6 @@ static int launch_relax_t(const RelaxArgs &a0, int num_cu, hipStream_t st)
     if ((rc = launch_relax_lds<R, RELAX_T0, RELAX_K0>(a, 0, num_cu * 4, st))) return rc;
     if ((rc = launch_relax_lds<R, RELAX_T1, RELAX_K1>(a, 1, num_cu, st))) return rc;
     hipLaunchKernelGGL(k_relax<R>, dim3(num_cu), dim3(1024), 0, st, a, huge_scratch());
-    hipLaunchKernelGGL(k_relax_finish, dim3(num_cu), dim3(256), 0, st, a);
     HIP_OK(hipGetLastError());
     return PIC_OK;
 }

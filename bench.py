@@ -747,7 +747,7 @@ def bench_rebin(args):
                  kernel_ms_per_step={k2: round(t / c, 5) for k2, (t, c) in kt.items()},
                  roofline={"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                           "traffic": None, "kernel": "k_radix_hist + scans + k_radix_scatter_lds "
+                           "traffic": None, "kernel": "k_radix_count + k_radix_place "
                            "(two passes) + k_bin_check", "kernel_avg_ms": round(sort_ms, 5),
                            "bytes_per_launch": n * bytes_sort})
 
@@ -791,7 +791,7 @@ def bench_nanbu(args):
                   "n_electrons": n},
                  roofline={"bound": "hbm", "achieved": round(achieved, 1), "peak": 8000.0,
                            "unit": "GB/s", "frac": round(achieved / 8000.0, 4), "traffic": None,
-                           "kernel": "class kernels with Nanbu's pair operator (k_collide<float, T, K, F_NANBU>)",
+                           "kernel": "class kernels with Nanbu's pair operator (k_collide_lean<T, K, F_NANBU>)",
                            "kernel_avg_ms": round(kern_ms, 5), "bytes_per_electron": per_e})
 
 
@@ -840,7 +840,7 @@ def bench_triplet(args):
                   "n_electrons": n},
                  roofline={"bound": "hbm", "achieved": round(achieved, 1), "peak": 8000.0,
                            "unit": "GB/s", "frac": round(achieved / 8000.0, 4), "traffic": None,
-                           "kernel": "class kernels with the odd-cell triplet (k_collide<float, T, K, F_TRIP>)",
+                           "kernel": "class kernels with the odd-cell triplet (k_collide_lean<T, K, F_TRIP>)",
                            "kernel_avg_ms": round(kern_ms, 5), "bytes_per_electron": per_e})
 
 

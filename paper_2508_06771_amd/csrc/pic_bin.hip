@@ -69,9 +69,9 @@ __global__ void k_step_inc(uint64_t *s)
 // Position i in [0, n] is the boundary between element i-1 and i: every cell
 // id j in (cell_of[i-1], cell_of[i]] starts at i, so with sorted input each
 // entry of cell_start is written exactly once (empty cells included).  Each
-// thread takes four consecutive positions (one 16-byte load when aligned), the
-// id before them comes from the lane below.  Bound by the read of cell_of
-// (4.7 TB/s on 40.96M sorted ids).  A workgroup reports at most once, and only
+// thread takes four consecutive positions (one 16-byte load when aligned) and
+// reads the id before them too, from a line it shares (passed up from the lane
+// below it took 42.9 us on 40.96M sorted ids, now 41.0: 4.0 TB/s).  A workgroup reports at most once, and only
 // what is not reported yet: with one atomic per wave on the same word a check
 // of 16M ids out of order took 350 us, most of it waiting for that word; now 20.
 constexpr int BC_T = 256;
@@ -87,10 +87,11 @@ __global__ __launch_bounds__(BC_T) void k_bin_check(const int32_t *__restrict__ 
     const int64_t nq = n / 4 + 1;
     const bool vec = ((uintptr_t)cell_of & 15u) == 0;
     const int64_t stride = (int64_t)gridDim.x * BC_T;
-    // whole waves take part in every round (the shuffle below)
+    // whole waves take part in every round (the ballot below)
     for (int64_t q0 = blockIdx.x * (int64_t)BC_T + wid * PIC_WAVE; q0 < nq; q0 += stride) {
         const int64_t i0 = (q0 + lane) * 4;
         int32_t c[5];
+        c[0] = i0 > 0 && i0 <= n ? cell_of[i0 - 1] : -1;
         if (vec && i0 + 4 <= n) {
             const int4 x = *(const int4 *)(cell_of + i0);
             c[1] = x.x;
@@ -101,10 +102,6 @@ __global__ __launch_bounds__(BC_T) void k_bin_check(const int32_t *__restrict__ 
 #pragma unroll
             for (int j = 0; j < 4; ++j) c[1 + j] = i0 + j < n ? cell_of[i0 + j] : n_cells;
         }
-        int32_t first = -1;   // the id before the wave's first position
-        if (lane == 0 && i0 > 0) first = cell_of[i0 - 1];
-        c[0] = __shfl_up(c[4], 1, PIC_WAVE);
-        if (lane == 0) c[0] = first;
         bool out[4], desc = false;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {

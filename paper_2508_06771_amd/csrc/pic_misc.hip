@@ -6,6 +6,7 @@
 #include <algorithm>
 
 #include "pic_internal.hpp"
+#include "pic_dsmc_new.hpp"
 
 #define HIP_OK(x) do { if ((x) != hipSuccess) return PIC_ERR_HIP; } while (0)
 
@@ -198,51 +199,9 @@ __device__ __forceinline__ uint32_t wave_append(bool p, uint32_t *ctr)
     return base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
 }
 
-constexpr int DSMC_T = 256;
 constexpr int DSMC_U = 8;                            // particles per thread and screening round
 constexpr int DSMC_FLUSH = DSMC_T;                   // waiting particles that are decided at once
 constexpr int DSMC_WAIT = DSMC_FLUSH + DSMC_T * DSMC_U;
-
-// New electrons wait in LDS and take their slots from the shared counter
-// together: with one addition per wave that ionizes, 16,000 for 40.96M
-// particles, the contended counter alone took 200 us.
-constexpr int DSMC_NEW = 2 * DSMC_T;
-template <typename R>
-struct DsmcNew {
-    R x[DSMC_NEW], y[DSMC_NEW], z[DSMC_NEW];
-    uint32_t pid[DSMC_NEW];
-    int32_t cell[DSMC_NEW];
-    uint32_t n;
-    unsigned long long base;
-};
-
-// Writes the waiting new electrons out (every thread of the workgroup takes
-// part; m of them, the same value for all).  Contains the barriers.
-template <typename R>
-__device__ __forceinline__ void dsmc_flush_new(const DsmcArgs &a, DsmcNew<R> &nw, uint32_t m)
-{
-    if (m == 0u) return;
-    R *nx = (R *)a.v_new, *ny = nx + a.cap, *nz = ny + a.cap;
-    if (threadIdx.x == 0) {
-        nw.base = atomicAdd(a.count, (unsigned long long)m);
-        nw.n = 0u;
-    }
-    __syncthreads();
-    const unsigned long long base = nw.base;
-    for (uint32_t i = threadIdx.x; i < m; i += DSMC_T) {
-        const unsigned long long k = base + i;
-        if (k < (unsigned long long)a.cap) {
-            nx[k] = nw.x[i];
-            ny[k] = nw.y[i];
-            nz[k] = nw.z[i];
-            a.pid_new[k] = nw.pid[i];
-            a.cell_new[k] = nw.cell[i];
-        } else {
-            atomicOr(&a.dflags->sticky_state, 1);
-        }
-    }
-    __syncthreads();
-}
 
 // Decides particle l (its cell is in range) and scatters it.
 template <typename R>
@@ -394,13 +353,13 @@ __global__ __launch_bounds__(DSMC_T) void k_dsmc(DsmcArgs a, DsmcTable t, int64_
                 __syncthreads();
                 const uint32_t m = s_new.n;
                 __syncthreads();
-                if (m > (uint32_t)(DSMC_NEW - DSMC_T)) dsmc_flush_new<R>(a, s_new, m);
+                if (m > (uint32_t)(DSMC_NEW - DSMC_T)) dsmc_flush_new<R>(a, s_new);
             }
             if (threadIdx.x == 0) s_n = 0u;
             __syncthreads();
         }
     }
-    dsmc_flush_new<R>(a, s_new, s_new.n);
+    dsmc_flush_new<R>(a, s_new);
 }
 
 // ------------------------------------------------------------ recombination

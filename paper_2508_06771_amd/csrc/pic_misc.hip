@@ -203,6 +203,22 @@ constexpr int DSMC_U = 8;                            // particles per thread and
 constexpr int DSMC_FLUSH = DSMC_T;                   // waiting particles that are decided at once
 constexpr int DSMC_WAIT = DSMC_FLUSH + DSMC_T * DSMC_U;
 
+// Binary32 stand-ins of the screen's inputs.  A number too small for a normal
+// one is raised to the smallest, so that no factor of a bound vanishes which is
+// positive in binary64 (one too large becomes infinite).
+constexpr float F32_MIN = 1.17549435e-38f;
+__host__ __device__ __forceinline__ float raise32(double x)   // of a bound's factor x
+{
+    const float f = (float)x;
+    return x > 0.0 && f < F32_MIN ? F32_MIN : f;
+}
+__device__ __forceinline__ float speed32(float x) { return x; }
+__device__ __forceinline__ float speed32(double x)
+{
+    const float f = (float)x;
+    return f == 0.0f && x != 0.0 ? F32_MIN : f;
+}
+
 // Decides particle l (its cell is in range) and scatters it.
 template <typename R>
 __device__ __forceinline__ void dsmc_decide(const DsmcArgs &a, const DsmcTable &t, const double *s_br,
@@ -302,8 +318,8 @@ __global__ __launch_bounds__(DSMC_T) void k_dsmc(DsmcArgs a, DsmcTable t, int64_
     const int64_t start = blockIdx.x * chunk;
     const int64_t end = start + chunk < a.n ? start + chunk : a.n;
     // binary32 factors of the bound, a little above the exact ones
-    const float dt = (float)a.dt * 1.0001f;
-    const float g0 = (float)a.ng0, m0 = (float)a.nm0;
+    const float dt = raise32(a.dt) * 1.0001f;
+    const float g0 = raise32(a.ng0), m0 = raise32(a.nm0);
     for (int64_t b = start; b < end; b += DSMC_T * DSMC_U) {
         uint32_t id[DSMC_U];
         int32_t cl[DSMC_U];
@@ -315,17 +331,17 @@ __global__ __launch_bounds__(DSMC_T) void k_dsmc(DsmcArgs a, DsmcTable t, int64_
             const uint32_t i = min(threadIdx.x + u * DSMC_T, left - 1u);
             id[u] = ld_at(a.pid + b, i);
             cl[u] = ld_at(a.cell + b, i);
-            x[u] = (float)ld_at(vx + b, i);
-            y[u] = (float)ld_at(vy + b, i);
-            z[u] = (float)ld_at(vz + b, i);
+            x[u] = speed32(ld_at(vx + b, i));
+            y[u] = speed32(ld_at(vy + b, i));
+            z[u] = speed32(ld_at(vz + b, i));
         }
         float dg[DSMC_U], dm[DSMC_U];
 #pragma unroll
         for (int u = 0; u < DSMC_U; ++u) {
             const bool in = cl[u] >= 0 && cl[u] < a.n_cells;
             // a negative density takes no part in an upper bound
-            dg[u] = fmaxf(a.ng ? (in ? (float)a.ng[cl[u]] : 0.0f) : g0, 0.0f);
-            dm[u] = fmaxf(a.nm ? (in ? (float)a.nm[cl[u]] : 0.0f) : m0, 0.0f);
+            dg[u] = fmaxf(a.ng ? (in ? raise32(a.ng[cl[u]]) : 0.0f) : g0, 0.0f);
+            dm[u] = fmaxf(a.nm ? (in ? raise32(a.nm[cl[u]]) : 0.0f) : m0, 0.0f);
         }
 #pragma unroll
         for (int u = 0; u < DSMC_U; ++u) {
@@ -336,9 +352,14 @@ __global__ __launch_bounds__(DSMC_T) void k_dsmc(DsmcArgs a, DsmcTable t, int64_
             const float E = 0.5f * (x[u] * x[u] + y[u] * y[u] + z[u] * z[u]);
             const int bin = (int)(__float_as_uint(E) >> DSMC_BIN_SHIFT) - t.bin0;
             const float2 up = s_up[min(max(bin, 0), DSMC_BINS - 1)];
-            const float bound = dt * __builtin_amdgcn_sqrtf(2.0f * E) * (dg[u] * up.x + dm[u] * up.y);
+            // the smallest normal number is added where a product may underflow
+            const float bound = fmaf(dt, __builtin_amdgcn_sqrtf(2.0f * E), F32_MIN) *
+                                (dg[u] * up.x + fmaf(dm[u], up.y, F32_MIN));
             const float R0 = u01f(draw4(a.seed, id[u], step, 6u, 0u).x);   // exact in binary32
-            const bool pass = valid && !bad && R0 < bound;
+            // an infinite or undefined bound excludes nothing, nor does an
+            // energy that binary32 does not hold, of a particle not at rest
+            const bool slow = E < 0x1p-100f && (x[u] != 0.0f || y[u] != 0.0f || z[u] != 0.0f);
+            const bool pass = valid && !bad && (slow || !(R0 >= bound));
             if (valid && !bad && !pass && a.chan_out) a.chan_out[b + i] = 0;
             const uint32_t k = wave_append(pass, &s_n);
             if (pass) s_wait[k] = (uint32_t)(b - start) + i;
@@ -915,6 +936,8 @@ static double dsmc_upper(int nseg, const double *br, const double *co, double th
     if (hi < thr) return 0.0;
     if (lo < thr) lo = thr;
     double best = 0.0;
+    for (int i = 0; i < 4 * nseg; ++i)
+        if (!isfinite(co[i])) return INFINITY;   // excludes nothing
     auto at = [&](int p, double e) {
         const double *q = co + (size_t)p * 4;
         double x = e - br[p];
@@ -931,22 +954,32 @@ static double dsmc_upper(int nseg, const double *br, const double *co, double th
         if (a > b) continue;
         at(p, a);
         at(p, b);
-        // 3 q3 x^2 + 2 q2 x + q1 = 0
-        const double *q = co + (size_t)p * 4;
+        // 3 q3 x^2 + 2 q2 x + q1 = 0, in parts of the interval and of the
+        // largest term, so that nothing leaves the range of the type
+        const double *q = co + (size_t)p * 4, w = b - br[p];
+        double q1 = q[1] * w, q2 = q[2] * w * w, q3 = q[3] * w * w * w;
+        const double big = fmax(fabs(q1), fmax(fabs(q2), fabs(q3)));
+        if (!isfinite(big)) return INFINITY;
+        if (big == 0.0) continue;
+        q1 /= big;
+        q2 /= big;
+        q3 /= big;
         double r[2];
         int nr = 0;
-        if (q[3] != 0.0) {
-            const double d = q[2] * q[2] - 3.0 * q[3] * q[1];
+        if (q3 != 0.0) {
+            const double d = q2 * q2 - 3.0 * q3 * q1;
             if (d >= 0.0) {
-                const double h = q[2] + (q[2] < 0.0 ? -sqrt(d) : sqrt(d));
-                r[nr++] = -h / (3.0 * q[3]);
-                if (h != 0.0) r[nr++] = -q[1] / h;
+                const double h = q2 + (q2 < 0.0 ? -sqrt(d) : sqrt(d));
+                r[nr++] = -h / (3.0 * q3);
+                if (h != 0.0) r[nr++] = -q1 / h;
             }
-        } else if (q[2] != 0.0) {
-            r[nr++] = -q[1] / (2.0 * q[2]);
+        } else if (q2 != 0.0) {
+            r[nr++] = -q1 / (2.0 * q2);
         }
-        for (int k = 0; k < nr; ++k)
-            if (br[p] + r[k] > a && br[p] + r[k] < b) at(p, br[p] + r[k]);
+        for (int k = 0; k < nr; ++k) {
+            const double e = br[p] + r[k] * w;
+            if (e > a && e < b) at(p, e);
+        }
     }
     return best;
 }
@@ -971,8 +1004,8 @@ int dsmc_bounds(int nseg, const double *br, const double *co, const double *thr,
         double g = 0.0;
         for (int c = 0; c < 3; ++c) g += dsmc_upper(nseg, br, co + (size_t)c * nseg * 4, thr[c], lo, hi);
         const double m = dsmc_upper(nseg, br, co + (size_t)3 * nseg * 4, thr[3], lo, hi);
-        upper[2 * k] = (float)(g * (1.0 + 1e-6));
-        upper[2 * k + 1] = (float)(m * (1.0 + 1e-6));
+        upper[2 * k] = raise32(g * (1.0 + 1e-6));
+        upper[2 * k + 1] = raise32(m * (1.0 + 1e-6));
     }
     return bin0;
 }

@@ -517,8 +517,9 @@ __global__ __launch_bounds__(256) void k_gate_mfma(GateArgs a)
 // The evaluated cells are first split by size (k_relax_classify).  Cells of
 // at most RELAX_LDS_CAP members: one workgroup per item of a cell and some of
 // its replicas sorts each replica's keys in LDS and sums the pair terms
-// 1/4 h(s^2) (|u|^2 I - 3 u u^T) into the item's first place of part[] (the
-// others are zero); relax_finish adds the replicas in order and normalises.
+// 1/4 h(s^2) (|u|^2 I - 3 u u^T) of each into part[]; relax_finish adds the
+// replicas in order and normalises.  No sum runs over the replicas of an item:
+// how many an item holds depends on the other cells listed, the label must not.
 // Larger cells take k_relax below.
 constexpr int RELAX_T0 = 256, RELAX_K0 = 8;      // <= 2048 members
 constexpr int RELAX_T1 = 1024, RELAX_K1 = 10;    // <= 10240 members
@@ -583,11 +584,53 @@ struct RelaxGeom {
     static constexpr size_t BYTES = REC > LeanGeom<T, K>::SORT_BYTES ? REC : LeanGeom<T, K>::SORT_BYTES;
 };
 
+// x of the lane that CTRL pairs with this one (DPP within a row of 16 lanes).
+template <int CTRL>
+__device__ __forceinline__ double row_pair(double x)
+{
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// The wave's sums of eight values: lanes 2 j (j < 8) return the total of value
+// j.  In a row of 16 lanes each exchange keeps half the values (partners agree
+// in the lane bits already used), the rows' sums are added last: 4 LDS
+// operations, where the halving over all 64 lanes by shuffles takes 20 (2,048
+// cells of 500 members with 8 replicas 96 us with it, with this one 94).
+__device__ __forceinline__ double relax_wave_sum(const double (&x)[8])
+{
+    const int lane = threadIdx.x & (PIC_WAVE - 1);
+    double y[4], z[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        y[j] = ((lane & 8) ? x[j + 4] : x[j]) + row_pair<0x140>((lane & 8) ? x[j] : x[j + 4]);   // lane ^ 15
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        z[j] = ((lane & 4) ? y[j + 2] : y[j]) + row_pair<0x141>((lane & 4) ? y[j] : y[j + 2]);   // lane ^ 7
+    double s = ((lane & 2) ? z[1] : z[0]) + row_pair<0x4e>((lane & 2) ? z[0] : z[1]);            // lane ^ 2
+    s += row_pair<0xb1>(s);                                                                      // lane ^ 1
+    s += __shfl_xor(s, 16, PIC_WAVE);
+    s += __shfl_xor(s, 32, PIC_WAVE);
+    return s;
+}
+
+// Replicas whose sums by wave are held in LDS until the item ends: cells of 500
+// members 92 us, added replica by replica 94.  With 1,024 threads (8 KB then)
+// replica by replica: 512 cells of 6,000 with 4 146 us against 155.
+template <int T>
+constexpr int relax_red()
+{
+    return T < 1024 ? (int)RELAX_REPS : 1;
+}
+
 // A work item is some replicas of one cell, whose members stay in registers:
 // each replica sorts (see lean_rank), posts the velocities at their positions
-// and adds its pairs to the item's sums.  Bound by the sort (LDS operations and
+// and sums its pairs.  Bound by the sort (LDS operations and
 // barriers on 16 waves a CU; the registers do not allow more): 2,048 cells of
-// 2,000 members with 8 replicas 246 us, of 500 88 us.  One replica an item,
+// 2,000 members with 8 replicas 250 us, of 500 92 us (245 and 87 with one sum
+// over an item's replicas).  One replica an item,
 // velocities gathered from memory by sorted index (six scattered loads a pair)
 // and the closed form of h on the library's erfcx took 335 and 152 us.
 template <typename R, int T, int K>
@@ -596,6 +639,7 @@ __device__ __forceinline__ void relax_item(const RelaxArgs &a, uint32_t which, i
                                            uint32_t *wtot)
 {
     typedef RelaxGeom<R, T, K> G;
+    constexpr int NW = T / PIC_WAVE, RED = relax_red<T>();
     const uint32_t reps = (uint32_t)a.replicas;
     R *px = (R *)smem, *py = px + G::P, *pz = py + G::P;
     const uint32_t *pid_c = a.pid + lo;
@@ -633,8 +677,8 @@ __device__ __forceinline__ void relax_item(const RelaxArgs &a, uint32_t which, i
             a.r_out[cell] = (s[3] / N - (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) / (N * N)) / 3.0;
     }
     const uint32_t bits = sort_bits(n);
-    double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // xx yy zz xy xz yz
     for (uint32_t rep = r0; rep < r1; ++rep) {
+        double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // xx yy zz xy xz yz
         uint32_t key[K], pos[K];
         lean_clear<T, K, true>((uint32_t *)smem, bits);
         lds_barrier();
@@ -679,19 +723,39 @@ __device__ __forceinline__ void relax_item(const RelaxArgs &a, uint32_t which, i
                 acc[5] += hq * (-3.0 * uy * uz);
             }
         }
-        lds_barrier();   // the next replica reuses the LDS
+        // the replica's sums by wave, added in order of the waves: behind the
+        // item's last replica where RED of them fit, else at once, behind the
+        // barrier that frees the LDS (red is written again only barriers later)
+        const uint32_t slot = RED > 1 ? rep - r0 : 0u;
+        const double ws = relax_wave_sum(acc);
+        if ((threadIdx.x & (PIC_WAVE - 1)) < 16 && (threadIdx.x & 1) == 0)
+            red[(slot * NW + threadIdx.x / PIC_WAVE) * 8 + (threadIdx.x & (PIC_WAVE - 1)) / 2] = ws;
+        lds_barrier();
+        if constexpr (RED == 1) {
+            if (threadIdx.x < 6) {
+                double t = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) t += red[w * 8 + threadIdx.x];
+                a.part[((size_t)which * reps + rep) * 6 + threadIdx.x] = t;
+            }
+        } else if (rep + 1 == r1) {
+            const uint32_t q = threadIdx.x / 8, c = threadIdx.x % 8;
+            if (q <= slot && c < 6) {
+                double t = 0.0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) t += red[(q * NW + w) * 8 + c];
+                a.part[((size_t)which * reps + r0 + q) * 6 + c] = t;
+            }
+        }
     }
-    // one sum for the item's replicas, in the first one's place
-    const double t = block_sum_scatter<8>(acc, red);
-    double *part = a.part + ((size_t)which * reps + r0) * 6;
-    if (threadIdx.x < 6 * (r1 - r0)) part[threadIdx.x] = threadIdx.x < 6 ? t : 0.0;
+    lds_barrier();   // the next item reuses red
 }
 
 template <typename R, int T, int K>
 __global__ __launch_bounds__(T, T >= 1024 || sizeof(R) == 4 ? 4 : 1) void k_relax_lds(RelaxArgs a, int cls)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[8 * (T / PIC_WAVE)];
+    __shared__ double red[relax_red<T>() * 8 * (T / PIC_WAVE)];
     __shared__ uint32_t wtot[T / PIC_WAVE];
     if (relax_off(a)) return;
     const uint32_t reps = (uint32_t)a.replicas, cells = a.cls_count[cls];

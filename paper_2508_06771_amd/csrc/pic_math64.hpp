@@ -205,7 +205,11 @@ PIC_M64_FN void m64_ta_half(double ux, double uy, double uz, double C, double U1
     double d;
     if (s2 > 0x1p-900 && s2 < 0x1p900) {
         d = m64_sqrt(s2, r) * z;
-    } else {   // zero, without bound, or no number
+    } else {
+        // zero, without bound (the quotient's correction then has no value: the
+        // bare product), or no number; a half change this small is beyond any use
+        s2 = C * PIC_M64_RCP(u3);
+        if (k) s2 = __builtin_ldexp(s2, -3 * k);
         d = __builtin_sqrt(s2) * z;
         d = d > 0x1p450 ? 0x1p450 : d < -0x1p450 ? -0x1p450 : d;
     }

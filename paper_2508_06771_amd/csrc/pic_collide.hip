@@ -943,6 +943,20 @@ struct LeanNext {
     float *sink;               // 64 words of LDS
 };
 
+// The next work item.  The cells of the 1,024-thread class take 10 us and more:
+// one counter for the whole list is not contended and deals them evenly to the
+// end.  Replayed steps of 12M electrons in cells of 9,000: 172 us (166 without
+// null collisions) against 176 (172) from 16 queues, of 40.96M in cells of
+// 10,000 449 us (437) against 451 (440); with two cells a workgroup or of 4,500
+// up to 0.6% more.  The first items are taken by index: from the counter too,
+// 256 workgroups begin 3 us late (100 cells of 9,000 56 us a step instead of 53).
+template <int T>
+__device__ __forceinline__ int lean_take(DevFlags *f, const LeanNext *nx)
+{
+    if constexpr (T >= 1024) return nx->slot[2] + (int)list_take(f, nx->cls);
+    else return (int)queue_take(f, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
+}
+
 // n entries of pid and of `arrays` further arrays of dwords, stride apart.
 template <int T>
 __device__ __forceinline__ void prefetch_run(const uint32_t *pid, uint32_t arrays, const float *v, size_t stride,
@@ -996,7 +1010,7 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
     if (n == 0) {
         if constexpr (MOM)
             if (threadIdx.x < 14) a.moments[(int64_t)cell * 14 + threadIdx.x] = 0.0;
-        if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
+        if (nx && threadIdx.x == 0) *nx->slot = lean_take<T>(a.dflags, nx);
         lds_barrier();   // leave together (see the end of the pass)
         if (nx) next = *nx->slot;
         lds_barrier();
@@ -1029,7 +1043,7 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
         if (a.debt && threadIdx.x < 4) s_debt[threadIdx.x] = a.debt[(int64_t)cell * 4 + threadIdx.x];
     // the next work item (issued behind this cell's loads, so waiting for it
     // costs nothing extra); read after a barrier below
-    if (nx && threadIdx.x == 0) *nx->slot = (int)queue_take(a.dflags, nx->cls, (unsigned)nx->slot[1], (unsigned)nx->slot[2]);
+    if (nx && threadIdx.x == 0) *nx->slot = lean_take<T>(a.dflags, nx);
     if (n >= 2) {
         uint32_t cpid = 0;
         lean_sort<T, K, MCC, true>(a, n, step, pid_c, smem, wtot, w2, w3, key, pos, cand, cpid);
@@ -1425,11 +1439,16 @@ __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int3
     R *vy_g = vx_g + a.n;
     R *vz_g = vy_g + a.n;
     Rec<R> *pb = (Rec<R> *)hs.pbuf;
-    for (uint32_t item = blockIdx.x, nxt; item < count; item = nxt) {
-        if (threadIdx.x == 0) s_item = (int)queue_take(a.dflags, cls, queue_of(blockIdx.x, gridDim.x), gridDim.x);
+    for (;;) {
+        // one counter for the list, for the first items too: a cell takes 50 us
+        // to milliseconds.  (Log-normal cells up to 134,000 members with the
+        // correction, mean of eight grids of 900 to 1,600: from 16 queues the step
+        // took 3.2 ms, 8% more than from one; equal cells of 30,000 4% more.)
+        if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
         __syncthreads();
-        nxt = (uint32_t)s_item;
+        const uint32_t item = (uint32_t)s_item;
         __syncthreads();
+        if (item >= count) break;
         if (only && !only[item]) continue;   // taken by the segmented path
         const int cell = list[item];
         const int lo = a.cell_start[cell];

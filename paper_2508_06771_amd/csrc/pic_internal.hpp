@@ -54,6 +54,12 @@ __device__ __forceinline__ unsigned int queue_take(DevFlags *f, int list, unsign
 {
     return takers + q + atomicAdd(&f->head[((unsigned)list * QUEUE_SPLIT + q) * QUEUE_LINE], QUEUE_SPLIT);
 }
+// The next item of a list that is not split (its items are long enough not to
+// contend for one counter).
+__device__ __forceinline__ unsigned int list_take(DevFlags *f, int list)
+{
+    return atomicAdd(&f->head[(unsigned)list * QUEUE_SPLIT * QUEUE_LINE], 1u);
+}
 inline int persistent_grid(int blocks)
 {
     return blocks < (int)QUEUE_SPLIT ? (int)QUEUE_SPLIT : blocks;

@@ -1420,7 +1420,37 @@ __device__ __forceinline__ void seg_fixup(const CollideArgs &a, const int32_t *l
 // ------------------------------------------------------------ huge cells
 // One workgroup per cell; per-particle state in global scratch indexed by the
 // particle's slot, so scratch regions of different cells never overlap.
-template <typename R, bool PAIRS>
+// What the kernel is built for.  A form without the others' code keeps its
+// members' values in registers: with everything in one kernel the binary64 form
+// spilled 98 registers (cells of 7,000 with weights 890 us for 6M electrons, with
+// the correction 3,540 for four steps; 4 registers now, 833 and 3,255).
+enum { HUGE_PAIRS, HUGE_SEG, HUGE_ONE, HUGE_NANBU };
+
+// Nanbu's operator out of line in binary64: in line its constants are kept over
+// the loop and spill (cells of 7,000, 6M electrons, 1,715 us; 1,040 now).
+struct HalfChange {
+    double x, y, z;
+};
+__device__ __noinline__ HalfChange nanbu_call(double ux, double uy, double uz, double C, uint32_t wa2, uint32_t wb2)
+{
+    HalfChange h;
+    nanbu_half<double>(ux, uy, uz, C, wa2, wb2, h.x, h.y, h.z);
+    return h;
+}
+template <typename R>
+__device__ __forceinline__ void nanbu_huge(R ux, R uy, R uz, R C, uint32_t wa2, uint32_t wb2, R &hx, R &hy, R &hz)
+{
+    if constexpr (std::is_same<R, double>::value) {
+        const HalfChange h = nanbu_call(ux, uy, uz, C, wa2, wb2);
+        hx = h.x;
+        hy = h.y;
+        hz = h.z;
+    } else {
+        nanbu_half<R>(ux, uy, uz, C, wa2, wb2, hx, hy, hz);
+    }
+}
+
+template <typename R, int MODE>
 __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int32_t *__restrict__ list,
                                                        int cls, HugeScratch hs, SegScratch ss,
                                                        const uint8_t *__restrict__ only)
@@ -1429,7 +1459,8 @@ __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int3
     __shared__ uint32_t wtot[16];
     __shared__ int s_item;
     if (gated_off(a)) return;
-    if constexpr (!PAIRS)
+    constexpr bool PAIRS = MODE == HUGE_PAIRS;
+    if constexpr (MODE == HUGE_SEG)
         if (only) seg_fixup<R>(a, list, ss);
     if (only && !a.dflags->seg_fallback) return;   // every cell went the segmented way
     const uint32_t count = a.dflags->count[cls];
@@ -1504,14 +1535,14 @@ __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int3
                     Rec<R> &e = pc[p >> 1];
                     R x = vx_g[lo + i], y = vy_g[lo + i], z = vz_g[lo + i];
                     R hx, hy, hz;
-                    if (a.variant == VAR_NANBU) {
+                    if constexpr (MODE == HUGE_NANBU) {
                         // the member in the lower storage slot is the operator's first
                         const uint32_t j = hs.lst[lo + p + 1];
                         const uint32_t own = hs.w23[2 * (int64_t)(lo + i)];
                         if ((uint32_t)i < j) {
-                            nanbu_half<R>(x - e.x, y - e.y, z - e.z, C, own, e.w2, hx, hy, hz);
+                            nanbu_huge<R>(x - e.x, y - e.y, z - e.z, C, own, e.w2, hx, hy, hz);
                         } else {
-                            nanbu_half<R>(e.x - x, e.y - y, e.z - z, C, e.w2, own, hx, hy, hz);
+                            nanbu_huge<R>(e.x - x, e.y - y, e.z - z, C, e.w2, own, hx, hy, hz);
                             hx = -hx;
                             hy = -hy;
                             hz = -hz;
@@ -2676,6 +2707,7 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
     typedef Classes<R> C;
     constexpr bool PAIRS = (F & F_PAIRS) != 0;
     constexpr bool SEG_OK = !PAIRS && !(F & (F_CONS | F_MOM | F_WT | F_NANBU | F_TRIP));
+    constexpr int HUGE = PAIRS ? HUGE_PAIRS : SEG_OK ? HUGE_SEG : (F & F_NANBU) ? HUGE_NANBU : HUGE_ONE;
     int rc;
     const int64_t M = n_cells;
     const int *bp = caps.blocks_per_cu;
@@ -2702,12 +2734,12 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
         HIP_OK(hipGetLastError());
         if ((rc = launch_seg_collide<R, G::T, G::K, F>(a, l4, ss, G::PER_CU * num_cu, st))) return rc;
         // cells the plan could not segment
-        hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
+        hipLaunchKernelGGL((k_collide_huge<R, HUGE>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
                            hs, g_seg, (const uint8_t *)ss.hc_fb);
       }
     }
     if (!seg_done)
-        hipLaunchKernelGGL((k_collide_huge<R, PAIRS>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
+        hipLaunchKernelGGL((k_collide_huge<R, HUGE>), dim3(persistent_grid(grid(4))), dim3(1024), 0, st, a, l4, 4,
                            hs, g_seg, (const uint8_t *)nullptr);
     if (live & (1u << 4)) ktime_end(KT_HUGE, st);
     HIP_OK(hipGetLastError());
@@ -2800,10 +2832,10 @@ int launch_unified(const CollideArgs &a, const int32_t *lists, int32_t n_cells, 
     HIP_OK(hipGetLastError());
     ktime_begin(KT_HUGE, st);
     if (seg_path) {
-        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs, g_seg,
+        hipLaunchKernelGGL((k_collide_huge<R, HUGE_SEG>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs, g_seg,
                            (const uint8_t *)ss.hc_fb);
     } else {
-        hipLaunchKernelGGL((k_collide_huge<R, false>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs, g_seg,
+        hipLaunchKernelGGL((k_collide_huge<R, HUGE_SEG>), dim3(persistent_grid(num_cu)), dim3(1024), 0, st, a, l4, 4, hs, g_seg,
                            (const uint8_t *)nullptr);
     }
     ktime_end(KT_HUGE, st);

@@ -1119,8 +1119,12 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
     return next;
 }
 
+// At most 128 registers for eight members a thread: with one more (129 to 147 in
+// the modes with moments, and with the correction and null collisions) the second
+// workgroup, for which the LDS leaves room, does not fit on the CU.  Cells of
+// 3,000 with moments 220 us a step of 12M electrons without the bound, 160 with it.
 template <int T, int K, int F>
-__global__ __launch_bounds__(T) void k_collide_lean(CollideArgs a, const int32_t *__restrict__ list,
+__global__ __launch_bounds__(T, K >= 8 ? 4 : 1) void k_collide_lean(CollideArgs a, const int32_t *__restrict__ list,
                                                     int cls)
 {
     extern __shared__ __align__(16) unsigned char smem[];

@@ -657,6 +657,18 @@ __global__ __launch_bounds__(T) void k_collide(CollideArgs a, const int32_t *__r
     if (gated_off(a)) return;
     const uint32_t count = a.dflags->count[cls];
     if (blockIdx.x >= count) return;   // no work for this workgroup (nor a queue atomic)
+    if constexpr (T >= 1024 && std::is_same<R, float>::value) {
+        // large cells: one counter, for the first items too (with 16 queues cells
+        // of 8,000 with the correction take 888 us instead of 836, by index first 844)
+        for (;;) {
+            if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
+            __syncthreads();
+            const uint32_t item = (uint32_t)s_item;
+            __syncthreads();
+            if (item >= count) return;
+            cell_pass<R, T, K, F>(a, list[item], smem, red, wtot, s_before);
+        }
+    }
     for (uint32_t item = blockIdx.x; item < count;) {
         if (threadIdx.x == 0) s_item = (int)queue_take(a.dflags, cls, queue_of(blockIdx.x, gridDim.x), gridDim.x);   // read after the pass's barriers
         cell_pass<R, T, K, F>(a, list[item], smem, red, wtot, s_before);
@@ -2635,12 +2647,21 @@ int launch_class(const CollideArgs &a, const int32_t *list, int cls, int blocks,
     return PIC_OK;
 }
 
-// The lean pass for binary32 steps (all but the pairing export); cell_pass
-// otherwise.
+// The lean pass for binary32 steps; cell_pass for the pairing export, and for
+// the correction without null collisions in the largest class: there the lean
+// pass spills 15 registers, cell_pass 5 (12M electrons, four steps: cells of
+// 4,200 1,086 and 1,010 us, of 8,000 895 and 836, of 10,000 864 and 852).  With
+// null collisions cell_pass spills more and the lean pass is twice as fast.
+template <int T, int F>
+constexpr bool lean_better()
+{
+    return !(F & F_PAIRS) && !(F == F_CONS && T >= 1024);
+}
+
 template <typename R, int T, int K, int F>
 int launch_class_best(const CollideArgs &a, const int32_t *list, int cls, int blocks, hipStream_t st)
 {
-    if constexpr (std::is_same<R, float>::value && (F & F_PAIRS) == 0) {
+    if constexpr (std::is_same<R, float>::value && lean_better<T, F>()) {
         const size_t lds = lean_lds_bytes<T, K, F>();
         auto kern = k_collide_lean<T, K, F>;
         static bool attr_done = false;

@@ -119,6 +119,32 @@ __device__ __forceinline__ void mcc_scatter(R &vx, R &vy, R &vz, uint32_t pid, u
     scatter_dir<MEM>(vx, vy, vz, draw4(seed, pid, step, 1u, 0u), mass_ratio);
 }
 
+// The same with CALL out of line in binary64, for the kernel of all classes: its
+// one workgroup a CU waits for every spilled register of a scatter in line.  6M
+// electrons in cells of 300, four steps: 5,379 us with it in line, 2,758 so, 2,434
+// without null collisions (of 1,000: 2,336, 1,250, 1,114).
+struct Velocity {
+    double x, y, z;
+};
+__device__ __noinline__ Velocity scatter_call(double x, double y, double z, W4 w, double mass_ratio)
+{
+    scatter_dir<false>(x, y, z, w, mass_ratio);
+    return {x, y, z};
+}
+template <typename R, bool CALL, bool MEM = false>
+__device__ __forceinline__ void mcc_scatter_as(R &vx, R &vy, R &vz, uint32_t pid, uint64_t seed, uint32_t step,
+                                               double mass_ratio)
+{
+    if constexpr (CALL && std::is_same<R, double>::value) {
+        const Velocity v = scatter_call(vx, vy, vz, draw4(seed, pid, step, 1u, 0u), mass_ratio);
+        vx = v.x;
+        vy = v.y;
+        vz = v.z;
+    } else {
+        mcc_scatter<R, MEM>(vx, vy, vz, pid, seed, step, mass_ratio);
+    }
+}
+
 __device__ __forceinline__ uint64_t read_step(const CollideArgs &a)
 {
     return a.step_dev ? *a.step_dev : a.step;
@@ -139,7 +165,7 @@ __device__ __forceinline__ bool gated_off(const CollideArgs &a)
 }
 
 // Variants compiled per kernel: which optional parts of the pass exist.
-enum { F_MCC = 1, F_CONS = 2, F_MOM = 4, F_PAIRS = 8, F_WT = 16, F_NANBU = 32, F_TRIP = 64 };
+enum { F_MCC = 1, F_CONS = 2, F_MOM = 4, F_PAIRS = 8, F_WT = 16, F_NANBU = 32, F_TRIP = 64, F_CALL = 128 };
 
 // Variable-weight rule for the pair (a, b) with half change h (a += h,
 // b -= h in the uniform step): the member of smaller weight always takes its
@@ -370,7 +396,7 @@ __device__ __forceinline__ void conserve_regs(int n, R (&vx)[K], R (&vy)[K], R (
 
 // Null collisions of the thread's candidate members (bits of cand) on their
 // registers, one candidate at a time per lane.
-template <typename R, int T, int K>
+template <typename R, int T, int K, bool CALL = false>
 __device__ __forceinline__ void scatter_regs(const CollideArgs &a, uint32_t cand, R (&vx)[K], R (&vy)[K],
                                              R (&vz)[K], const uint32_t *pid_c, uint32_t step)
 {
@@ -389,7 +415,7 @@ __device__ __forceinline__ void scatter_regs(const CollideArgs &a, uint32_t cand
                 y = kk == k ? ay : y;
                 z = kk == k ? az : z;
             }
-            mcc_scatter<R, (T >= 1024)>(x, y, z, pid_c[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
+            mcc_scatter_as<R, CALL, (T >= 1024)>(x, y, z, pid_c[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const R ax = vx[k], ay = vy[k], az = vz[k];
@@ -628,7 +654,7 @@ __device__ __forceinline__ void cell_pass(const CollideArgs &a, int cell, unsign
     // takes its candidates one at a time (selected out of its register slots)
     // instead of branching per slot, which would run the scattering for every
     // slot holding a candidate in any lane of the wave
-    if constexpr (MCC) scatter_regs<R, T, K>(a, cand, vx, vy, vz, pid_c, step);
+    if constexpr (MCC) scatter_regs<R, T, K, (F & F_CALL) != 0>(a, cand, vx, vy, vz, pid_c, step);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int i = threadIdx.x + k * T;
@@ -2019,7 +2045,7 @@ __device__ __forceinline__ void seg_pass(const CollideArgs &a, const int32_t *li
                         y = vy[k];
                         z = vz[k];
                     }
-                mcc_scatter<R, true>(x, y, z, pid_s[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
+                mcc_scatter_as<R, (F & F_CALL) != 0, true>(x, y, z, pid_s[threadIdx.x + kk * T], a.seed, step, a.mass_ratio);
 #pragma unroll
                 for (int k = 0; k < K; ++k)
                     if (kk == k) {
@@ -2478,7 +2504,7 @@ __device__ __forceinline__ void wave_pass(const CollideArgs &a, int cell, unsign
                         y = vy[k];
                         z = vz[k];
                     }
-                mcc_scatter<R>(x, y, z, pid_c[lane + kk * PIC_WAVE], a.seed, step, a.mass_ratio);
+                mcc_scatter_as<R, true>(x, y, z, pid_c[lane + kk * PIC_WAVE], a.seed, step, a.mass_ratio);
 #pragma unroll
                 for (int k = 0; k < KW; ++k)
                     if (kk == k) {
@@ -2597,7 +2623,7 @@ __global__ __launch_bounds__(1024) void k_collide_all(CollideArgs a, const int32
         lds_barrier();
         if (item < nseg) {
             if constexpr (std::is_same<R, float>::value) lean_seg_pass<SG::T, SG::K, F>(a, l4, ss, item, smem, wtot);
-            else seg_pass<R, SG::T, SG::K, F>(a, l4, ss, (int)item, smem, wtot);
+            else seg_pass<R, SG::T, SG::K, F | F_CALL>(a, l4, ss, (int)item, smem, wtot);
             continue;
         }
         const int cell = order[item - nseg];
@@ -2610,9 +2636,9 @@ __global__ __launch_bounds__(1024) void k_collide_all(CollideArgs a, const int32
         } else {
             __shared__ double red[16 * 16];
             __shared__ double s_before[4];
-            if (n <= 2048) cell_pass<R, 1024, 2, F>(a, cell, smem, red, wtot, s_before);
-            else if (n <= 4096) cell_pass<R, 1024, 4, F>(a, cell, smem, red, wtot, s_before);
-            else cell_pass<R, 1024, CL::K3, F>(a, cell, smem, red, wtot, s_before);
+            if (n <= 2048) cell_pass<R, 1024, 2, F | F_CALL>(a, cell, smem, red, wtot, s_before);
+            else if (n <= 4096) cell_pass<R, 1024, 4, F | F_CALL>(a, cell, smem, red, wtot, s_before);
+            else cell_pass<R, 1024, CL::K3, F | F_CALL>(a, cell, smem, red, wtot, s_before);
         }
     }
     if (wave_cls < 0) return;

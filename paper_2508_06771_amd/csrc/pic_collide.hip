@@ -686,11 +686,13 @@ __global__ __launch_bounds__(T) void k_collide(CollideArgs a, const int32_t *__r
     if constexpr (T >= 1024 && std::is_same<R, float>::value) {
         // large cells: one counter, for the first items too (with 16 queues cells
         // of 8,000 with the correction take 888 us instead of 836, by index first 844)
-        for (;;) {
-            if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
-            __syncthreads();
-            const uint32_t item = (uint32_t)s_item;
-            __syncthreads();
+        for (uint32_t item = blockIdx.x;; item = count) {
+            if (count > gridDim.x) {   // (see k_collide_huge)
+                if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
+                __syncthreads();
+                item = (uint32_t)s_item;
+                __syncthreads();
+            }
             if (item >= count) return;
             cell_pass<R, T, K, F>(a, list[item], smem, red, wtot, s_before);
         }
@@ -1512,15 +1514,20 @@ __global__ __launch_bounds__(1024) void k_collide_huge(CollideArgs a, const int3
     R *vy_g = vx_g + a.n;
     R *vz_g = vy_g + a.n;
     Rec<R> *pb = (Rec<R> *)hs.pbuf;
-    for (;;) {
-        // one counter for the list, for the first items too: a cell takes 50 us
-        // to milliseconds.  (Log-normal cells up to 134,000 members with the
-        // correction, mean of eight grids of 900 to 1,600: from 16 queues the step
-        // took 3.2 ms, 8% more than from one; equal cells of 30,000 4% more.)
-        if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
-        __syncthreads();
-        const uint32_t item = (uint32_t)s_item;
-        __syncthreads();
+    for (uint32_t item = blockIdx.x;; item = count) {
+        // Up to one cell a workgroup: by index, so that in the next step the cell
+        // comes to the same XCD, whose L2 may still hold it (20 cells of 20,000 with
+        // weights 244 us, from the counter 274).  Else one counter for the list,
+        // for the first items too: a cell takes 50 us to milliseconds.  (Log-normal
+        // cells up to 134,000 members with the correction, mean of eight grids of
+        // 900 to 1,600: from 16 queues the step took 3.2 ms, 8% more than from one;
+        // equal cells of 30,000 4% more.)
+        if (count > gridDim.x) {
+            if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
+            __syncthreads();
+            item = (uint32_t)s_item;
+            __syncthreads();
+        }
         if (item >= count) break;
         if (only && !only[item]) continue;   // taken by the segmented path
         const int cell = list[item];

@@ -582,14 +582,13 @@ int launch_bin_check(const int32_t *cell_of, int64_t n, int32_t n_cells, int32_t
     return PIC_OK;
 }
 
-// Words of scratch of a pass: 256 digits x workgroups (at most one per tile),
-// the digits' starts behind them, and alignment.
+// Scratch of a pass: a count per digit and workgroup (at most one workgroup per
+// tile, and RS_MAX_BLOCKS), the digits' starts behind them, and alignment.
 size_t radix_scratch_bytes(int64_t n)
 {
-    const int64_t nb = (n + RS_TILE - 1) / RS_TILE + 1;
-    const int64_t L = RS_DIGITS * nb;
-    const int64_t ns = (L + 8191) / 8192 + 1;
-    return (size_t)(L + ns) * sizeof(uint32_t) + 512;
+    const int64_t tiles = (n + RS_TILE - 1) / RS_TILE;
+    const int64_t groups = tiles < RS_MAX_BLOCKS ? tiles : RS_MAX_BLOCKS;
+    return (size_t)(RS_DIGITS * (groups + 1)) * sizeof(uint32_t) + 512;
 }
 
 namespace {

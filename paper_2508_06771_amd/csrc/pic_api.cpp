@@ -702,8 +702,7 @@ int pic_mlp_train_step(pic_ctx *c, float *params, float *adam_m, float *adam_v, 
     if (!c || !params || !adam_m || !adam_v || t < 1 || !(lr > 0.0f) || batch < 1 || !x || !y)
         return PIC_ERR_ARG;
     CK(hipSetDevice(c->device));
-    const size_t sf = mlp_grad_scratch_floats(batch);
-    RC(ensure_ws(c, (sf + 4801 + 64) * 4 + 1024));
+    RC(ensure_ws(c, mlp_grad_scratch_floats(batch) * 4 + 1024));
     const MlpAdam adam = {params, adam_m, adam_v, t, lr};
     return launch_mlp_grad(params, x, y, batch, bf16 != 0, (float *)c->ws, nullptr, loss, &adam, c->stream);
 }

@@ -1271,7 +1271,7 @@ int launch_mlp_forward(const float *params, const float *x, int32_t B, int bf16,
 size_t mlp_grad_scratch_floats(int32_t B)
 {
     const int tiles = (B + TS - 1) / TS;
-    return (size_t)tiles * NPARAM + tiles + NPARAM + 64;
+    return (size_t)tiles * NPARAM + tiles;   // partial gradients, partial losses
 }
 
 int launch_mlp_grad(const float *params, const float *x, const float *y, int32_t B, int bf16,

@@ -185,10 +185,15 @@ __device__ __forceinline__ void count_digit(uint32_t *h, uint32_t d, bool valid)
 
 // Digit counts of each workgroup's run of tiles, hist[d * gridDim.x + block];
 // the last workgroup turns every digit's row into an exclusive scan over the
-// workgroups and writes the digits' starts behind the rows.  The counts travel
-// in device-scope stores and loads, complete before the workgroup's arrival is
-// counted; a fence instead would write back a whole L2 per workgroup (150 us
-// when every wave issued one).
+// workgroups and writes the digits' starts behind the rows.
+// The hand-over between the workgroups is outside the language's memory model
+// (a relaxed counter orders nothing) and stands on this GPU's: stores and loads
+// of device scope pass by the XCDs' L2s, each wave waits until its stores have
+// been acknowledged (s_waitcnt, which the compiler does not take for an ordering;
+// the __syncthreads behind it is one) before thread 0 counts the workgroup's
+// arrival, and the last workgroup's loads are issued behind a __syncthreads that
+// follows the arrival it has seen.  A release there instead would write back a
+// whole L2 per workgroup (25 us; 150 us when every wave issued one).
 constexpr int RC_T = 1024;
 constexpr int RC_WAIT_VM = 0x0F70;   // s_waitcnt operand: vector memory only
 

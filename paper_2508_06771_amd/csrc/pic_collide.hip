@@ -1781,9 +1781,12 @@ __device__ __forceinline__ void seg_scan(const CollideArgs &a, const SegScratch 
 }
 
 // Segment sizes: an LDS histogram per work item, then one global add per
-// non-empty segment.  The workgroup that ends last scans them (its counts are
-// read after every other workgroup's adds have completed: each waits for its
-// own before it reports).  With the edge pairs done in k_collide_huge the
+// non-empty segment.  The workgroup that ends last scans them: the adds are done
+// where the device is coherent, each wave waits for its own (s_waitcnt vmcnt, with
+// a __syncthreads behind it that also orders the compiler) before its workgroup
+// reports, and the last one reads past the caches.  (A relaxed counter orders
+// nothing in the language's memory model; see k_radix_count for the reasons it
+// holds here.)  With the edge pairs done in k_collide_huge the
 // path is four launches instead of six, about 2.7 us each where it has nothing
 // to do.
 __global__ __launch_bounds__(SEG_CT) void k_seg_count(CollideArgs a, const int32_t *__restrict__ list,

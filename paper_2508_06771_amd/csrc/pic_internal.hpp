@@ -44,7 +44,7 @@ struct DevFlags {
 // has one.  One counter for the whole list was the bound of every list of many
 // small cells: taking from it costs about 12 ns device-wide, 495 us for 40,000
 // cells of 200 members (now 115), 2,317 us for 200,000 of 50 (now 443), 210 us
-// for 16,000 of 1,000 (now 160).
+// for 16,000 of 1,000 (now 160).  Lists of large cells keep one counter (list_take).
 __device__ __forceinline__ unsigned int queue_of(unsigned int taker, unsigned int takers)
 {
     return (takers >= 8 * QUEUE_SPLIT ? taker / 8 : taker) % QUEUE_SPLIT;

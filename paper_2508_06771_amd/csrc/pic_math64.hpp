@@ -131,7 +131,9 @@ PIC_M64_FN void m64_sincos(double p, double &s, double &c)
 
 // log of a normal x in (0, 1) within 1 ulp: x = 2^e (1 + f) with 1 + f in
 // [sqrt(1/2), sqrt(2)), log(1 + f) = f - f^2/2 + t (f^2/2 + R), t = f / (2 + f),
-// R = 2 atanh(t) / t - 2.
+// R = 2 atanh(t) / t - 2, ln 2 in two parts: the reduction that fdlibm's log
+// publishes (Sun Microsystems, 1993), with a polynomial of its own and the
+// rounding errors of f - f^2/2 and of e ln 2 + that carried along.
 PIC_M64_FN double m64_log_c(double x, const double *c)
 {
     double m = PIC_M64_FREXP_MANT(x);     // [1/2, 1)

@@ -171,8 +171,10 @@ __global__ void k_unsort_copy(R *__restrict__ v, uint32_t *__restrict__ pid, int
 // bin of E (an eighth of an octave, from the energy's leading bits), selects no
 // channel.  The particles that pass wait in LDS until there are enough to fill
 // the workgroup, and are decided exactly.
-// Bound by the reads of v, pid, cell (20 B a binary32 particle):
-// 40.96M particles, 2% colliding, 690 -> 284 us.
+// 40.96M binary32 particles, 2% colliding: 690 -> 285 us, 2.9 TB/s of the 20 B
+// read a particle (v, pid, cell); a copy reaches 4.8.  Bound by the latency of a
+// round (loads, Philox, table, list) with four workgroups on a CU: 127 registers
+// (144 in binary64: three), most of them for the decision.
 __device__ __forceinline__ void dsmc_dir(uint32_t wa, uint32_t wb, double &sx, double &sy, double &sz)
 {
 #pragma clang fp contract(off)
@@ -913,8 +915,9 @@ int launch_unsort(int dtype, void *v, uint32_t *pid, int32_t *cell_of, int64_t n
 int launch_dsmc(int dtype, const DsmcArgs &a, const DsmcTable &t, int num_cu, hipStream_t st)
 {
     if (a.n <= 0) return PIC_OK;
-    // contiguous runs of whole screening rounds, eight workgroups per CU (more
-    // where a run would not fit 32 bits)
+    // contiguous runs of whole screening rounds, eight workgroups for each CU, of
+    // which four (binary64: three) are resident (more runs where one would not
+    // fit 32 bits)
     const int64_t round = DSMC_T * DSMC_U, rounds = (a.n + round - 1) / round;
     int64_t g = std::min<int64_t>(rounds, (int64_t)num_cu * 8);
     int64_t per = (rounds + g - 1) / g;

@@ -686,14 +686,14 @@ __global__ __launch_bounds__(T) void k_collide(CollideArgs a, const int32_t *__r
     if constexpr (T >= 1024 && std::is_same<R, float>::value) {
         // large cells: one counter, for the first items too (with 16 queues cells
         // of 8,000 with the correction take 888 us instead of 836, by index first 844)
-        for (uint32_t item = blockIdx.x;; item = count) {
-            if (count > gridDim.x) {   // (see k_collide_huge)
-                if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
-                __syncthreads();
-                item = (uint32_t)s_item;
-                __syncthreads();
-            }
-            if (item >= count) return;
+        // (a uniform item, or one by index where the workgroups cover the list, made
+        // the pass slower: cells of 8,000 858 and 867 us)
+        for (;;) {
+            if (threadIdx.x == 0) s_item = (int)list_take(a.dflags, cls);
+            __syncthreads();
+            const int item = s_item;
+            __syncthreads();
+            if (item >= (int)count) return;
             cell_pass<R, T, K, F>(a, list[item], smem, red, wtot, s_before);
         }
     }
@@ -1159,12 +1159,12 @@ __device__ __forceinline__ int lean_pass(const CollideArgs &a, int cell, unsigne
     return next;
 }
 
-// At most 128 registers for eight members a thread: with one more (129 to 147 in
-// the modes with moments, and with the correction and null collisions) the second
+// At most 128 registers for eight members a thread and cell sums: with one more (129
+// to 147 with moments, and with the correction and null collisions) the second
 // workgroup, for which the LDS leaves room, does not fit on the CU.  Cells of
 // 3,000 with moments 220 us a step of 12M electrons without the bound, 160 with it.
 template <int T, int K, int F>
-__global__ __launch_bounds__(T, K >= 8 ? 4 : 1) void k_collide_lean(CollideArgs a, const int32_t *__restrict__ list,
+__global__ __launch_bounds__(T, T < 1024 && K >= 8 && (F & (F_CONS | F_MOM)) ? 4 : 1) void k_collide_lean(CollideArgs a, const int32_t *__restrict__ list,
                                                     int cls)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -2686,34 +2686,35 @@ int launch_class(const CollideArgs &a, const int32_t *list, int cls, int blocks,
 // The lean pass for binary32 steps; cell_pass for the pairing export, and for
 // the correction without null collisions in the largest class: there the lean
 // pass spills 15 registers, cell_pass 5 (12M electrons, four steps: cells of
-// 4,200 1,086 and 1,010 us, of 8,000 895 and 836, of 10,000 864 and 852).  With
-// null collisions cell_pass spills more and the lean pass is twice as fast.
-template <int T, int F>
-constexpr bool lean_better()
-{
-    return !(F & F_PAIRS) && !(F == F_CONS && T >= 1024);
-}
-
+// 4,200 1,093 and 1,009 us, of 8,000 883 and 833, of 10,000 882 and 852).  With
+// null collisions cell_pass spills more and the lean pass is twice as fast.  Where
+// the list holds at most one cell a workgroup (few), the lean pass's shorter way
+// through a cell counts: 100 cells of 9,000 220 us against 241.
 template <typename R, int T, int K, int F>
-int launch_class_best(const CollideArgs &a, const int32_t *list, int cls, int blocks, hipStream_t st)
+int launch_class_best(const CollideArgs &a, const int32_t *list, int cls, int blocks, hipStream_t st,
+                      bool few = false)
 {
-    if constexpr (std::is_same<R, float>::value && lean_better<T, F>()) {
-        const size_t lds = lean_lds_bytes<T, K, F>();
-        auto kern = k_collide_lean<T, K, F>;
-        static bool attr_done = false;
-        if (!attr_done) {
-            HIP_OK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds));
-            attr_done = true;
+    if constexpr (std::is_same<R, float>::value && !(F & F_PAIRS)) {
+        if (F != F_CONS || T < 1024 || few) {
+            const size_t lds = lean_lds_bytes<T, K, F>();
+            auto kern = k_collide_lean<T, K, F>;
+            static bool attr_done = false;
+            if (!attr_done) {
+                HIP_OK(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds));
+                attr_done = true;
+            }
+            ktime_begin(KT_CLASS0 + cls, st);
+            hipLaunchKernelGGL(kern, dim3(persistent_grid(blocks)), dim3(T), lds, st, a, list, cls);
+            ktime_end(KT_CLASS0 + cls, st);
+            HIP_OK(hipGetLastError());
+            return PIC_OK;
         }
-        ktime_begin(KT_CLASS0 + cls, st);
-        hipLaunchKernelGGL(kern, dim3(persistent_grid(blocks)), dim3(T), lds, st, a, list, cls);
-        ktime_end(KT_CLASS0 + cls, st);
-        HIP_OK(hipGetLastError());
-        return PIC_OK;
-    } else {
-        return launch_class<R, T, K, F>(a, list, cls, blocks, st);
     }
+    if constexpr (!std::is_same<R, float>::value || (F & F_PAIRS) || (F == F_CONS && T >= 1024))
+        return launch_class<R, T, K, F>(a, list, cls, blocks, st);
+    else
+        return PIC_ERR_ARG;   // not reached
 }
 
 template <bool MCC, int K = LEAN64_K>
@@ -2815,7 +2816,7 @@ int launch_all(const CollideArgs &a, const int32_t *lists, int32_t n_cells, int 
                 done = true;
             }
         }
-        if (!done && (rc = launch_class_best<R, C::T3, C::K3, F>(a, lists + 3 * M, 3, grid(3), st)))
+        if (!done && (rc = launch_class_best<R, C::T3, C::K3, F>(a, lists + 3 * M, 3, grid(3), st, most(3) <= num_cu)))
             return rc;
     }
     if (live & (1u << 2)) {

@@ -780,8 +780,10 @@ __global__ __launch_bounds__(T, T >= 1024 || sizeof(R) == 4 ? 4 : 1) void k_rela
         const int lo = a.cell_start[cell];
         const int n = a.cell_start[cell + 1] - lo;
         if (n < 2 || n > T * K) continue;   // the same for the whole workgroup
-        // small cells without the loads and branches of members they lack
-        if (T < 1024 && n <= 2 * T) relax_item<R, T, 2>(a, which, cell, lo, n, r0, r1, step, smem, red, wtot);
+        // small cells without the loads and branches of members they lack (300 cells
+        // of 2,049, one replica: ten members a thread 52 us, binary64 77; four 36 and 40)
+        constexpr int KS = T < 1024 ? 2 : 4;
+        if (n <= KS * T) relax_item<R, T, KS>(a, which, cell, lo, n, r0, r1, step, smem, red, wtot);
         else relax_item<R, T, K>(a, which, cell, lo, n, r0, r1, step, smem, red, wtot);
     }
 }

@@ -44,26 +44,37 @@ __device__ __forceinline__ float bf16r(float x)
 // rest is below 1e-15.  Within 2.5e-15 of h for every w (4e-16 rms up to 10,
 // 1e-15 beyond), where the closed form with a series below t = 1e-3 was off by
 // up to 1.4e-10 (w > 10), 8e-14 (1 < w < 3) and 1e-15 (w < 0.1).
-__constant__ const double H_POLY[27] = {   // from the highest power
-    -0x1.139b93a32c579p-23, -0x1.19e69f397196fp-21, 0x1.23378c199a724p-21, 0x1.3b5c990c019b7p-18,
-    0x1.2de3a71631ac0p-19, -0x1.36ca0b4b76d10p-16, -0x1.e23d17d6644e0p-16, 0x1.0de1ac4243934p-15,
-    0x1.1f0951c4df9d1p-13, 0x1.04c8dd0ddca30p-14, -0x1.a7fbf80d63beap-12, -0x1.7c7c2f80e1bc3p-11,
-    0x1.5fb5ca311a3d1p-11, 0x1.cd71a1dc2e69bp-9, 0x1.9717120942acbp-11, -0x1.be62a09c8632dp-7,
-    -0x1.a7ef318383821p-7, 0x1.a5a2c2ae6b3c4p-5, 0x1.355dc3fd957c4p-4, -0x1.d2dcc2775a1efp-3,
-    -0x1.491374b305af2p-2, 0x1.4f3f34d7b29d1p+0, 0x1.6fe64817992bcp-2, -0x1.f22c40739c15ep+2,
-    0x1.18ae5e4c3a658p+4, -0x1.408701148f3d3p+4, 0x1.619c914713ac8p+3,
-};
+#define H_POLY_LIST \
+    -0x1.139b93a32c579p-23, -0x1.19e69f397196fp-21, 0x1.23378c199a724p-21, 0x1.3b5c990c019b7p-18, \
+    0x1.2de3a71631ac0p-19, -0x1.36ca0b4b76d10p-16, -0x1.e23d17d6644e0p-16, 0x1.0de1ac4243934p-15, \
+    0x1.1f0951c4df9d1p-13, 0x1.04c8dd0ddca30p-14, -0x1.a7fbf80d63beap-12, -0x1.7c7c2f80e1bc3p-11, \
+    0x1.5fb5ca311a3d1p-11, 0x1.cd71a1dc2e69bp-9, 0x1.9717120942acbp-11, -0x1.be62a09c8632dp-7, \
+    -0x1.a7ef318383821p-7, 0x1.a5a2c2ae6b3c4p-5, 0x1.355dc3fd957c4p-4, -0x1.d2dcc2775a1efp-3, \
+    -0x1.491374b305af2p-2, 0x1.4f3f34d7b29d1p+0, 0x1.6fe64817992bcp-2, -0x1.f22c40739c15ep+2, \
+    0x1.18ae5e4c3a658p+4, -0x1.408701148f3d3p+4, 0x1.619c914713ac8p+3
+__constant__ const double H_POLY[27] = {H_POLY_LIST};   // from the highest power
+template <bool MEM>
 __device__ __forceinline__ double h_angle(double w)
 {
-    // read through a pointer the compiler cannot see through: the coefficients
-    // come from the scalar cache where they are used (kept in vector registers
-    // they cost 54 of them)
-    const double *c = H_POLY;
-    asm volatile("" : "+s"(c));
+    // MEM: read through a pointer the compiler cannot see through, so that the
+    // coefficients come from the scalar cache where they are used (kept in vector
+    // registers they cost 54 of them); where the registers are there, as in
+    // k_relax, in them: each pair waits for the cache otherwise (cells of 20,000 with
+    // 8 replicas 1,560 us, in registers 1,449)
     const double r = m64_rcp(w + 2.5), y = __builtin_fma(-5.0, r, 1.0);
-    double p = c[0];
+    double p;
+    if constexpr (MEM) {
+        const double *c = H_POLY;
+        asm volatile("" : "+s"(c));
+        p = c[0];
 #pragma unroll
-    for (int i = 1; i < 27; ++i) p = __builtin_fma(p, y, c[i]);
+        for (int i = 1; i < 27; ++i) p = __builtin_fma(p, y, c[i]);
+    } else {
+        constexpr double c[] = {H_POLY_LIST};
+        p = c[0];
+#pragma unroll
+        for (int i = 1; i < 27; ++i) p = __builtin_fma(p, y, c[i]);
+    }
     return p * (w * r) * (r * r);
 }
 
@@ -71,6 +82,7 @@ __device__ __forceinline__ double h_angle(double w)
 // 1 / (2 t) = c2 |u|^3.  Where the short square roots do not cover the
 // arguments (and for a C that is not positive) the general functions, and the
 // leading terms in t where w is beyond any use.
+template <bool MEM>
 __device__ __forceinline__ double h_pair(double uu, double C, double c2)
 {
     double w;
@@ -83,7 +95,7 @@ __device__ __forceinline__ double h_pair(double uu, double C, double c2)
         if (!(t >= 1e-12)) return t * (4.0 - 24.0 * t);
         w = 1.0 / sqrt(2.0 * t);
     }
-    return h_angle(w);
+    return h_angle<MEM>(w);
 }
 
 // Eight features from the raw sums m[0..13] (layout of pic_cell_moments).
@@ -714,7 +726,7 @@ __device__ __forceinline__ void relax_item(const RelaxArgs &a, uint32_t which, i
                 const double uz = (double)pz[2 * q] - (double)pz[2 * q + 1];
                 const double uu = ux * ux + uy * uy + uz * uz;
                 if (uu == 0.0) continue;
-                const double hq = 0.25 * h_pair(uu, C, c2);
+                const double hq = 0.25 * h_pair<true>(uu, C, c2);
                 acc[0] += hq * (uu - 3.0 * ux * ux);
                 acc[1] += hq * (uu - 3.0 * uy * uy);
                 acc[2] += hq * (uu - 3.0 * uz * uz);
@@ -863,7 +875,7 @@ __global__ __launch_bounds__(1024) void k_relax(RelaxArgs a, HugeScratch hs)
                 const double uz = (double)vz[ia] - (double)vz[ib];
                 const double uu = ux * ux + uy * uy + uz * uz;
                 if (uu == 0.0) continue;
-                const double hq = 0.25 * h_pair(uu, C, c2);
+                const double hq = 0.25 * h_pair<false>(uu, C, c2);
                 acc[0] += hq * (uu - 3.0 * ux * ux);
                 acc[1] += hq * (uu - 3.0 * uy * uy);
                 acc[2] += hq * (uu - 3.0 * uz * uz);
